@@ -565,7 +565,6 @@ int cholqr_pass(dion_state* st, const Group& g, int row0, int batch, long long r
   }
   if (shift_rel > 0.f) HIPCHK(launch_shift_diagonal(tab, NSLOTS, batch, r, rp, shift_rel, s, gate_slot));
   if (!small) HIPCHK(launch_pad_identity(tab, NSLOTS, batch, SLOT_C, r, rp, s, gate_slot));
-  if (rank_tol > 0.f) HIPCHK(launch_rank_threshold(tab, NSLOTS, batch, rp, rank_tol, s));
   // (W needs no clearing: its part above the block diagonal was zeroed at init and nothing ever writes there; the
   // rest is overwritten in full by the factorisation kernels, the merges below or the first-order factor)
   // Second pass: the input is already orthonormal to about 1e-5, so its Gram matrix is I + E with tiny E
@@ -579,6 +578,10 @@ int cholqr_pass(dion_state* st, const Group& g, int row0, int batch, long long r
                                       use_stream));
     c_nsplit = 1;
   }
+  // (the thresholds come from the diagonal of this pass' whole Gram matrix, which an adaptive pass has in SLOT_C only now: read
+  // before, they were what the pass before had left there, and a column that it had found dependent, exactly zero by
+  // now, could be taken for a pivot of zero, a breakdown)
+  if (rank_tol > 0.f) HIPCHK(launch_rank_threshold(tab, NSLOTS, batch, rp, rank_tol, s));
   base.status_slot = skip;
   // blocked right-looking Cholesky, one fused launch per 64-wide panel.  The kernel gets the addresses of
   // its buffers as arguments: a look-up in the pointer table would cost it one more memory round trip.

@@ -138,6 +138,51 @@ def test_double_dion_stage_one_breakdown_and_dependent_column_in_stage_two():
     assert float(np.min(np.abs(np.sum(V2.astype(np.float64) * ref["V2"], axis=0)))) > 1 - 1e-3
 
 
+@pytest.mark.parametrize("r2,links", [(192, 128), (512, 256)])       # a launch per panel, and all panels in one launch
+def test_column_dropped_in_the_second_pass_stays_dropped_in_the_last(r2, links):
+    # B2 V2 built column by column: V2 is the first columns of the identity, M2 holds the columns, stage 1 adds nothing to
+    # speak of.  Chains z_0 = q_0, z_l = c q_(l-1) + s q_l with s^2 > RANK_TOL have condition (c / s)^l: in fp32 the pivots
+    # of the first pass are rounding noise from the fourth link on.  Behind them, in later panels, a column that lies
+    # in the span of each chain: where the noise was positive the first pass takes it for a column of its own, the second
+    # finds it dependent.  A few longer chains leave the second pass' result away from orthonormal, so that the last
+    # pass is not cut short and has to drop those columns again.  (What the noise does differs from seed to seed: seeds that
+    # do not get there, or whose second pass leaves more than the last one's pivot bounds allow, say nothing here.)
+    m, n, r1 = 1024, 512, 8
+    chains = [(4, 0.04)] * ((links - 36) // 4) + [(6, 0.06)] * 6
+    checked = 0
+    for seed in range(10):
+        q = np.linalg.qr(np.random.default_rng(seed).standard_normal((m, r2)))[0]
+        coef = np.eye(r2)
+        pos = 0
+        for k, (length, s) in enumerate(chains):
+            for l in range(1, length):
+                coef[:, pos + l] = 0.0
+                coef[pos + l - 1, pos + l], coef[pos + l, pos + l] = np.sqrt(1.0 - s * s), s
+            coef[:, links + k] = 0.0
+            coef[pos + length - 1, links + k] = 1.0
+            pos += length
+        z = (q @ coef).astype(np.float32)
+        dp = DoubleProblem([(m, n)], r1, r2, False, "f32", v2_raw=[np.eye(n, r2, dtype=np.float32)], warm=False)
+        dp.M2[0][:, :r2].copy_(torch.from_numpy(z))
+        dp.upload([inputs.gaussian((m, n), 1e-9, 3, 1, 0, 0)])
+        st1, st2 = dp.step()
+        debug = lambda which: B.dion_debug_buffer(dp.s2, 0, which).cpu().numpy().astype(np.float64)
+        p1, p2, p = (debug(w)[:, :r2] for w in (B.DEBUG_P1, B.DEBUG_Z, B.DEBUG_P))     # of the three passes
+        keep1, keep2 = (np.abs(x).max(axis=0) > 0 for x in (p1, p2))
+        ev = np.linalg.eigvalsh(p2[:, keep2].T @ p2[:, keep2])
+        defect = np.linalg.norm(p2.T @ p2 - np.diag(keep2.astype(float)))
+        print("r2", r2, "seed", seed, "dropped in the first pass", int(np.sum(~keep1)), "in the second", int(np.sum(keep1 & ~keep2)),
+              "defect after it %.2e" % defect, "eigenvalues %.2e to %.2e" % (ev[0], ev[-1]), st2, flush=True)
+        if not (np.any(keep1 & ~keep2) and defect > 1e-3 and ev[0] > 0.1 and ev[-1] < 10):     # (pivots lie between these)
+            continue
+        checked += 1
+        assert st1 == (0, -1) and st2 == (0, -1)
+        null = debug(B.DEBUG_NULL).reshape(-1)[:r2] != 0
+        assert np.all(null >= ~keep2)
+        assert np.abs(p.T @ p - np.diag((~null).astype(float))).max() < 1e-5     # the bound of the other fp32 tests
+    assert checked >= 3
+
+
 def test_double_dion_cold_start_moves_the_weights_from_the_first_step():
     # from M2 = 0 the buffer of stage 2 has rank r1, 2 r1, ...: the step uses the rank that is there.  While the buffer
     # fills up, the independent columns of B2 V2 are badly conditioned among themselves (squared relative distances down
