@@ -183,8 +183,9 @@ void plan_gram(Group& g, bool lean) {
     // 1490 -> 1461.  (Below 64 tiles neither the split nor the copy pays; a batch's last round is not split.)
     const long long tiles256 = g.r % 256 == 0 ? (std::min(g.m, g.n) / 256) * (g.r / 256) * g.count : 0;
     const bool big_tiles = tiles256 >= 128 || (g.count == 1 && tiles256 >= 64 && std::min(g.m, g.n) >= 4096);
-    if (!big_tiles && tiles < 512) g.k12_splitk = (int)std::min<long long>(8, (512 + tiles - 1) / tiles);
     g.direct12 = big_tiles && g.m * g.n * 2 < (1ll << 32);
+    // (a copy that the direct-load kernels cannot address leaves the products to the 128 x 128 tiles, which want their split)
+    if (!g.direct12 && tiles < 512) g.k12_splitk = (int)std::min<long long>(8, (512 + tiles - 1) / tiles);
   }
 }
 

@@ -110,6 +110,17 @@ def test_workspace_bytes_sweep(lib):
         assert B.dion_workspace_bytes([shapes[i] for i in perm], B.DION_G_BF16, B.DION_MATH_BF16) == ref
 
 
+def test_workspace_holds_the_split_where_the_copy_is_too_large(lib):
+    """One matrix with 64 to 127 tiles of 256 x 256 whose bf16 copy of M + G is beyond the direct-load kernels' 32-bit
+    offsets: its products run on 128 x 128 tiles, 256 to 511 of them, and are split in two over the contraction.  The
+    workspace then holds two partial results on top of the fp32 and bf16 operand buffers."""
+    for (m, n, r) in [(16384, 131072, 256), (4096, 524288, 1024)]:
+        mr, nr = m * r, n * r
+        buffers = 4 * (2 * mr + 2 * nr) + 2 * 7 * nr + 2 * m * n
+        for g in (B.DION_G_F32, B.DION_G_BF16):
+            assert B.dion_workspace_bytes([(m, n, r)], g, B.DION_MATH_BF16) >= buffers + 4 * 2 * nr
+
+
 def test_null_state_is_rejected(lib):
     assert lib.dion_step(None, None, None, None, None, 4, 4, 2, 0.9, 0.1, None) == B.DION_EINVAL
     assert lib.dion_step_batched(None, 0, None, None, None, None, None, None, None, 0.9, 0.1, None) == B.DION_EINVAL
