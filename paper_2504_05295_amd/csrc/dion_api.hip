@@ -47,6 +47,18 @@ int pick_update_variant(long long M, long long N, long long K, long long batch) 
   if (N < 64) return VAR_SMALL_NARROW;
   return VAR_SMALL_RAGGED;
 }
+// The products with M + G in the general core, the contraction in `split` parts: 128 x 128 tiles (half the operand traffic of
+// 64 x 64) where they give every compute unit one workgroup and waste no more than a fifth against the smaller ones at the
+// edges.  By the call's batch: one of 64 matrices of 1024 x 1024, r = 256, in fp32 takes 382 us on the batch's tiles, 262 on
+// its own; one of 24 of 1500 x 1500, r = 250, 497 and 308.
+int product_variant(long long M, long long N, long long K, long long batch, long long split) {
+  const long long ts = ((M + 63) / 64) * ((N + 63) / 64) * batch, tb = ((M + 127) / 128) * ((N + 127) / 128) * batch;
+  const bool exact = M % 64 == 0 && N % 64 == 0 && K % 64 == 0;
+  if (M >= 128 && N >= 128 && K >= 64 && 10 * 4 * tb <= 12 * ts && tb * split >= 256)
+    return exact && M % 128 == 0 && N % 128 == 0 ? VAR_BIG : VAR_BIG_RAGGED;
+  if (exact) return VAR_SMALL;
+  return M < 64 || K < 64 ? VAR_SMALL_CHECKED : N < 64 ? VAR_SMALL_NARROW : VAR_SMALL_RAGGED;
+}
 void plan_chol_grid(int cus, int batch, int nb, int* pr, int* pc, int* chain) {
   *pr = 0; *pc = 0; *chain = 0;
   if (cus < 1 || batch < 1 || nb < 4 || nb > 128) return;
@@ -114,23 +126,19 @@ int padded_rank(int64_t r) { return (int)((r + CHOL_NB - 1) / CHOL_NB * CHOL_NB)
 
 // The products with M + G have a thin output (m x r or n x r) and a long contraction, and off the large-tile path often too
 // few tiles to give every compute unit one (1111 x 139: 54 of 64 x 64).  The contraction is split until there are about two
-// workgroups per compute unit, each with a contraction of 128 at least, which hide each other's loads; a launch more adds
-// the partial results up (5-7 us).  128 x 128 tiles (half the operand traffic) where the split gives every compute unit one of
-// those and they waste no more than a fifth against the smaller ones at the edges.  Measured, us a step, without the
-// split / 64 x 64 tiles only / as it is:  5003 x 2999 r = 375 bf16 mode 616 / 582 / 505;  1111 x 1733 r = 139 fp32
-// 293 / 222 / 222;  7936 x 354 r = 34 (transposed) 365 / 162 / 162;  2048 x 2048 r = 512 fp32 417 / 390 / 389;  two layers of
-// d = 768 740 / 653 / 652.  (A contraction of 256 or 512 at least: 228 / 239 us at 1111 x 1733; three or four workgroups
-// per compute unit: no difference.)
+// workgroups per compute unit, each with a contraction of 128 at least, which hide each other's loads; the partial results
+// are added up by the kernel that takes the column norms or by a launch more.  Measured when the split came in (the partial
+// results added up by a launch of their own), us a step, without it / with it on 64 x 64 tiles only / with both tiles:
+// 5003 x 2999 r = 375 bf16 mode 616 / 582 / 505;  1111 x 1733 r = 139 fp32 293 / 222 / 222;  7936 x 354 r = 34 (transposed)
+// 365 / 162 / 162;  2048 x 2048 r = 512 fp32 417 / 390 / 389;  two layers of d = 768 740 / 653 / 652.  (A contraction
+// of 256 or 512 at least: 228 / 239 us at 1111 x 1733; three or four workgroups per compute unit: no difference.)
+// The split belongs to the group, whose workspace holds the partial results; the tiles are those of each call's batch.
 ProductPlan plan_product(long long M, long long N, long long K, long long batch, bool may_split) {
   ProductPlan p;
-  const long long ts = ((M + 63) / 64) * ((N + 63) / 64) * batch, tb = ((M + 127) / 128) * ((N + 127) / 128) * batch;
   const long long most = may_split ? std::min<long long>(16, std::max<long long>(1, K / 128)) : 1;
-  const bool big = M >= 128 && N >= 128 && K >= 64 && 10 * 4 * tb <= 12 * ts && tb * most >= 256;
-  const bool exact = M % 64 == 0 && N % 64 == 0 && K % 64 == 0;
-  if (big) p.variant = exact && M % 128 == 0 && N % 128 == 0 ? VAR_BIG : VAR_BIG_RAGGED;
-  else if (exact) p.variant = VAR_SMALL;
-  else p.variant = M < 64 || K < 64 ? VAR_SMALL_CHECKED : N < 64 ? VAR_SMALL_NARROW : VAR_SMALL_RAGGED;
-  const long long tiles = big ? tb : ts;
+  p.variant = product_variant(M, N, K, batch, most);
+  const long long bt = p.variant == VAR_BIG || p.variant == VAR_BIG_RAGGED ? 128 : 64;
+  const long long tiles = ((M + bt - 1) / bt) * ((N + bt - 1) / bt) * batch;
   const long long split = std::min(most, (512 + tiles - 1) / tiles);
   const long long kps = ((K + split - 1) / split + 63) / 64 * 64;
   p.splitk = (int)((K + kps - 1) / kps);
@@ -878,7 +886,9 @@ hipError_t run_product(const RowCtx& c, ProductFn fn, const ProductPlan& p, Gemm
     a.E.slot = SLOT_KPART;
     a.E.split_stride = (long long)align_up((size_t)a.M * a.N, 4);
   }
-  const hipError_t e = fn(p.variant, c.bf16, c.gbf16, a, c.batch, c.s);
+  // (the whole group: as planned, with the split that was allowed for, of which rounding may have left fewer parts)
+  const int variant = c.batch == c.g->count ? p.variant : product_variant(a.M, a.N, a.K, c.batch, p.splitk);
+  const hipError_t e = fn(variant, c.bf16, c.gbf16, a, c.batch, c.s);
   if (e != hipSuccess || p.splitk == 1) return e;
   return finish_split(c, slot_out, a.E.split_stride, p.splitk, pending);
 }

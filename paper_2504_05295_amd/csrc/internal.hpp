@@ -78,6 +78,8 @@ enum { VAR_BIG = 0, VAR_SMALL = 1, VAR_SMALL_CHECKED = 2, VAR_BIG_RAGGED = 3, VA
 // have leading dimensions that are multiples of 8 whenever the dimensions are multiples of 64.
 int pick_variant(long long M, long long N, long long K, long long batch, bool aligned);
 int pick_update_variant(long long M, long long N, long long K, long long batch);   // the same for gemm_k5
+// the same for gemm_k1 / gemm_k2 with the contraction in `split` parts
+int product_variant(long long M, long long N, long long K, long long batch, long long split);
 
 // GEMM families (each defined in its own translation unit).  `bf16`: MMA operand type.
 hipError_t gemm_k1(int variant, bool bf16, bool gbf16, GemmArgs g, int batch, hipStream_t s);   // A = M+G (KC), B = fp32 KS

@@ -18,6 +18,11 @@
 #include "../../include/dion.h"
 #include "../../paper_2504_05295_amd/csrc/inv_tree_order.hpp"
 
+// (dion_api.hip; variant 0 and 3 are the 128 x 128 tiles, 1 and 4 the 64 x 64 ones, internal.hpp)
+namespace dion {
+int product_variant(long long M, long long N, long long K, long long batch, long long split);
+}
+
 static int failures = 0;
 #define EXPECT(cond)                                                   \
   do {                                                                 \
@@ -85,6 +90,19 @@ int main() {
     EXPECT(dion_step(nullptr, nullptr, nullptr, nullptr, nullptr, 8, 8, 2, 0.9f, 0.1f, nullptr) == DION_EINVAL);
     EXPECT(dion_destroy_state(nullptr) == DION_OK || dion_destroy_state(nullptr) == DION_EINVAL);
   }
+  // Tiles of the products with M + G: those of the call's batch, so that one matrix of a state of many is not left with the
+  // few large tiles of the whole batch; never 128 x 128 where they are fewer than a round of workgroups.
+  EXPECT(dion::product_variant(512, 128, 512, 64, 2) == 0);
+  EXPECT(dion::product_variant(512, 128, 512, 1, 2) == 1);
+  EXPECT(dion::product_variant(1500, 250, 1500, 24, 2) == 3);
+  EXPECT(dion::product_variant(1500, 250, 1500, 1, 2) == 4);
+  for (long long m : {128, 500, 512, 1500, 4096})
+    for (long long r : {128, 250, 512})
+      for (long long batch : {1, 3, 64})
+        for (long long split : {1, 2, 16}) {
+          const int v = dion::product_variant(m, r, m, batch, split);
+          EXPECT((v != 0 && v != 3) || (m + 127) / 128 * ((r + 127) / 128) * batch * split >= 256);
+        }
   // tile order of the triangular inverse
   size_t orders = 0;
   const int group_counts[] = {1, 2, 3, 4, 5, 7, 8, 15, 16, 35, 63, 64, 100, 255, 256};

@@ -63,6 +63,27 @@ def test_batched_equals_single_and_is_deterministic():
             assert np.array_equal(u, w)            # same tile configuration => batched == single, bit for bit
 
 
+@pytest.mark.parametrize("shape,count", [((512, 512, 128), 64), ((500, 520, 130), 64)])
+def test_one_matrix_of_a_state_of_many(shape, count):
+    # The products with M + G take 128 x 128 tiles for the whole batch and 64 x 64 ones for one matrix, over the same parts of
+    # the contraction: the same sums in the same order where no dimension has a remainder, in another one at the last
+    # slab of a ragged contraction.
+    x0, q0 = inputs.weight(*shape[:2]), inputs.right_factor_raw(shape[1], shape[2])
+    a, b = (GpuProblem([shape] * count, False, "f32", x0=[x0] * count, q_raw=[q0] * count) for _ in range(2))
+    for t in range(2):
+        g = inputs.gradient(shape[0], shape[1], t)
+        a.upload_grads([g] * count)
+        b.upload_grads([g] * count)
+        before = b.host(0)
+        assert a.step(MU, ETA) == (0, -1)
+        assert b.step(MU, ETA, batched=False) == (0, -1)
+        if shape[0] % 128 == 0:
+            for u, v in zip(a.host(count - 1), b.host(0)):
+                assert np.array_equal(u, v)
+        rep, _ = one_step_report(b, 0, *before, g, MU, ETA, "lapack")
+        assert rep["X"] <= 1e-4 and rep["M"] <= 1e-4 and rep["dX"] <= 2e-4 and rep["dM"] <= 2e-4 and rep["orth"] <= 1e-5, (t, rep)
+
+
 def test_breakdown_is_reported_and_state_untouched():
     m, n, r = 256, 192, 32
     q_raw = inputs.right_factor_raw(n, r)
