@@ -274,8 +274,9 @@ __global__ void __launch_bounds__(256) colnorm_partial_kernel(void* const* table
   float* part = (float*)table[(size_t)blockIdx.z * nslots + SLOT_SPART];
   __shared__ float red[4][64];
   const int cx = threadIdx.x & 63, ry = threadIdx.x >> 6;
-  const int col = blockIdx.x * 64 + cx;
-  const long long row_begin = (long long)blockIdx.y * COLNORM_ROWS;
+  const int ncb = (r + 63) / 64, chunk = blockIdx.x / ncb;
+  const int col = blockIdx.x % ncb * 64 + cx;
+  const long long row_begin = (long long)chunk * COLNORM_ROWS;
   const int nrows = (int)min((long long)COLNORM_ROWS, rows - row_begin);
   float acc = 0.f;
   if (col < r) {
@@ -289,7 +290,7 @@ __global__ void __launch_bounds__(256) colnorm_partial_kernel(void* const* table
   }
   red[ry][cx] = acc;
   __syncthreads();
-  if (ry == 0 && col < r) part[(long long)blockIdx.y * r + col] = (red[0][cx] + red[1][cx]) + (red[2][cx] + red[3][cx]);
+  if (ry == 0 && col < r) part[(long long)chunk * r + col] = (red[0][cx] + red[1][cx]) + (red[2][cx] + red[3][cx]);
 }
 // The same on a matrix that still is nsplit partial results `stride` floats apart in slot_part: adds them up in the order of
 // the splits, stores the sum to slot_out and takes its squares on the way, which saves a launch and a pass over the matrix
@@ -302,8 +303,9 @@ __global__ void __launch_bounds__(1024) colnorm_sum_partial_kernel(void* const* 
   float* part = (float*)table[(size_t)blockIdx.z * nslots + SLOT_SPART];
   __shared__ float red[16][64];
   const int cx = threadIdx.x & 63, ry = threadIdx.x >> 6;
-  const int col = blockIdx.x * 64 + cx;
-  const long long row_begin = (long long)blockIdx.y * COLNORM_ROWS;
+  const int ncb = (r + 63) / 64, chunk = blockIdx.x / ncb;
+  const int col = blockIdx.x % ncb * 64 + cx;
+  const long long row_begin = (long long)chunk * COLNORM_ROWS;
   const int nrows = (int)min((long long)COLNORM_ROWS, rows - row_begin);
   float acc = 0.f;
   if (col < r) {
@@ -332,7 +334,7 @@ __global__ void __launch_bounds__(1024) colnorm_sum_partial_kernel(void* const* 
     float sum = 0.f;
 #pragma unroll
     for (int u = 0; u < 16; u += 4) sum += (red[u][cx] + red[u + 1][cx]) + (red[u + 2][cx] + red[u + 3][cx]);
-    part[(long long)blockIdx.y * r + col] = sum;
+    part[(long long)chunk * r + col] = sum;
   }
 }
 static_assert(COLNORM_ROWS == 128, "colnorm_sum_partial_kernel: sixteen rows at a time, eight times");
@@ -377,11 +379,12 @@ hipError_t launch_colnorm_final(void* const* table, int nslots, int batch, int n
 hipError_t launch_colnorm(void* const* table, int nslots, int batch, int slot_in, long long rows, int r, hipStream_t s, int* pending,
                           PendingSum sum) {
   const int nchunks = (int)((rows + COLNORM_ROWS - 1) / COLNORM_ROWS);
+  const unsigned blocks = (unsigned)nchunks * ((r + 63) / 64);   // (on one axis: the others end at 65536)
   if (sum.nsplit > 1)
-    hipLaunchKernelGGL(colnorm_sum_partial_kernel, dim3((r + 63) / 64, nchunks, batch), dim3(1024), 0, s, table, nslots, SLOT_KPART, slot_in,
+    hipLaunchKernelGGL(colnorm_sum_partial_kernel, dim3(blocks, 1, batch), dim3(1024), 0, s, table, nslots, SLOT_KPART, slot_in,
                        rows, r, sum.nsplit, sum.stride);
   else
-    hipLaunchKernelGGL(colnorm_partial_kernel, dim3((r + 63) / 64, nchunks, batch), dim3(256), 0, s, table, nslots, slot_in, rows, r);
+    hipLaunchKernelGGL(colnorm_partial_kernel, dim3(blocks, 1, batch), dim3(256), 0, s, table, nslots, slot_in, rows, r);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_colnorm_final(table, nslots, batch, nchunks, r, s, pending);
@@ -396,14 +399,16 @@ __global__ void __launch_bounds__(256) scale_cols_kernel(void* const* table, int
                                                          int nchunks) {
   void* const* tab = table + (size_t)blockIdx.z * nslots;
   __shared__ float dsh[256];
+  const int ncb = (r + 255) / 256, cb = blockIdx.x % ncb;
+  const long long rb = blockIdx.x / ncb;
   if (nchunks > 0) {
     const float* part = (const float*)tab[SLOT_SPART];
-    const int c = blockIdx.x * 256 + threadIdx.x;
+    const int c = cb * 256 + threadIdx.x;
     if (c < r) {
       const float nrm = sqrtf(sum_planes<float>(part + c, r, nchunks));
       const float dv = 1.0f / (nrm + COLNORM_EPS);
       dsh[threadIdx.x] = dv;
-      if (blockIdx.y == 0) {
+      if (rb == 0) {
         ((float*)tab[SLOT_S])[c] = nrm;
         ((float*)tab[SLOT_D])[c] = dv;
       }
@@ -418,9 +423,9 @@ __global__ void __launch_bounds__(256) scale_cols_kernel(void* const* table, int
   const float* d = (const float*)tab[SLOT_D];
   const int* nullmask = null_slot >= 0 ? (const int*)tab[null_slot] : nullptr;
   // a block covers 32 rows x 256 columns; a thread owns 4 consecutive columns (or fewer at a ragged edge)
-  const int col = blockIdx.x * 256 + (threadIdx.x & 63) * 4;
+  const int col = cb * 256 + (threadIdx.x & 63) * 4;
   if (col >= r) return;
-  const long long row_end = min(rows, ((long long)blockIdx.y + 1) * 32);
+  const long long row_end = min(rows, (rb + 1) * 32);
   // this thread's four factors (two separate reads: one pointer to either memory would be a generic one, and an offset
   // taken from it before the column index is added leaves the LDS aperture)
   f32x4_t dv = {0.f, 0.f, 0.f, 0.f};
@@ -444,7 +449,7 @@ __global__ void __launch_bounds__(256) scale_cols_kernel(void* const* table, int
     for (int e = 0; e < 4; ++e)
       if (e < ncol) { keep_old[e] = nullmask[col + e] != 0; any_old = any_old || keep_old[e]; }
   }
-  for (long long row0 = (long long)blockIdx.y * 32 + (threadIdx.x >> 6); row0 < row_end; row0 += 32) {
+  for (long long row0 = rb * 32 + (threadIdx.x >> 6); row0 < row_end; row0 += 32) {
     f32x4_t v[8], o[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
@@ -493,7 +498,9 @@ __global__ void __launch_bounds__(256) scale_cols_kernel(void* const* table, int
 }
 hipError_t launch_scale_cols(void* const* table, int nslots, int batch, int slot_in, int slot_out, long long rows, int r,
                              int status_slot, int slot_out16, int slot_in16, hipStream_t s, int null_slot, int nchunks) {
-  hipLaunchKernelGGL(scale_cols_kernel, dim3((r + 255) / 256, (unsigned)((rows + 31) / 32), batch), dim3(256), 0, s, table, nslots,
+  // (row and column blocks on one axis: the others end at 65536, which is 2097152 rows)
+  const unsigned blocks = (unsigned)((rows + 31) / 32) * ((r + 255) / 256);
+  hipLaunchKernelGGL(scale_cols_kernel, dim3(blocks, 1, batch), dim3(256), 0, s, table, nslots,
                      slot_in, slot_out, rows, r, status_slot, slot_out16, slot_in16, null_slot, nchunks);
   return hipGetLastError();
 }

@@ -23,3 +23,27 @@ def test_edges_of_tiles(shape, g_bf16, math):
         rep, _ = one_step_report(gp, 0, x_in, m_in, q_in, gp.grad_as_f32(g, g_bf16), MU, ETA, "lapack")
         assert rep["X"] <= tol and rep["M"] <= tol and rep["dX"] <= 2 * tol and rep["dM"] <= 2 * tol, (shape, t, rep)
         assert rep["orth"] <= (1e-5 if math == "f32" else 1e-3), (shape, t, rep)
+
+
+@pytest.mark.parametrize("lazy", [False, True])
+def test_more_blocks_of_rows_than_a_second_grid_axis_takes(lazy):
+    # 65625 blocks of 32 rows when the factor's columns are scaled; 65536 is the end of a grid's second axis
+    from oracle import dion_oracle as orc
+    from gpu_harness import relf
+    shape = (9, 2100000, 4)
+    gp = GpuProblem([shape], True, "f32")
+    g = gp.grads_np(0)[0]
+    x_in, m_in, q_in = gp.host()
+    gp.upload_grads([g])
+    g32 = gp.grad_as_f32(g, True)
+    if lazy:
+        assert gp.lazy_step(MU, ETA, True) == (0, -1)
+        ref = orc.lazy_dion_step(x_in, g32, m_in, q_in, MU, ETA, True, "lapack")
+        q_ref = ref["V"]
+    else:
+        assert gp.step(MU, ETA) == (0, -1)
+        ref = orc.dion_step(x_in, g32, m_in, q_in, MU, ETA, "lapack")
+        q_ref = ref["Q"]
+    X, M, Q = gp.host()
+    # (the update itself, eta sqrt(m / n) / sqrt(n) an entry, is what X's last bit resolves here: the factor is compared instead)
+    assert relf(X, ref["X"]) <= 1e-4 and relf(M, ref["M"]) <= 1e-4 and relf(Q, q_ref) <= 1e-4
