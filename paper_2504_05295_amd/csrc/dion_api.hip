@@ -32,9 +32,7 @@ int pick_variant(long long M, long long N, long long K, long long batch, bool al
     return (tiles >= 256 || !small_ok) ? VAR_BIG : VAR_SMALL;
   }
   if (small_ok) return VAR_SMALL;
-  if (M < 64 || K < 64) return VAR_SMALL_CHECKED;
-  if (N < 64) return VAR_SMALL_NARROW;
-  return VAR_SMALL_RAGGED;
+  return M < 64 || N < 64 || K < 64 ? VAR_SMALL_CHECKED : VAR_SMALL_RAGGED;
 }
 // The fused update: 128 x 64 tiles where they give every compute unit one at least (a third less operand traffic than
 // 64 x 64), whose k-slab of 32 also takes smaller ranks.
@@ -43,9 +41,7 @@ int pick_update_variant(long long M, long long N, long long K, long long batch) 
   const bool exact = M % 64 == 0 && N % 64 == 0 && K % 32 == 0;
   if (M >= 128 && N >= 64 && K >= 32 && tiles >= 256) return exact && M % 128 == 0 ? VAR_BIG : VAR_BIG_RAGGED;
   if (exact && K % 64 == 0) return VAR_SMALL;
-  if (M < 64 || K < 64) return VAR_SMALL_CHECKED;
-  if (N < 64) return VAR_SMALL_NARROW;
-  return VAR_SMALL_RAGGED;
+  return M < 64 || N < 64 || K < 64 ? VAR_SMALL_CHECKED : VAR_SMALL_RAGGED;
 }
 // The products with M + G in the general core, the contraction in `split` parts: 128 x 128 tiles (half the operand traffic of
 // 64 x 64) where they give every compute unit one workgroup and waste no more than a fifth against the smaller ones at the
@@ -149,8 +145,8 @@ ProductPlan plan_product(long long M, long long N, long long K, long long batch,
 GramPlan plan_gram_rows(const Group& g, int64_t rows) {
   GramPlan gp;
   gp.variant = pick_variant(g.r, g.r, rows, g.count, true);
-  const int bt = (gp.variant == VAR_BIG || gp.variant == VAR_BIG_RAGGED) ? 128 : 64;
-  const int bk = (gp.variant == VAR_BIG || gp.variant == VAR_BIG_RAGGED) ? 32 : 64;
+  const int bt = (gp.variant == VAR_BIG) ? 128 : 64;
+  const int bk = (gp.variant == VAR_BIG) ? 32 : 64;
   const long long t1 = (g.r + bt - 1) / bt;
   const long long tiles = t1 * (t1 + 1) / 2 * g.count;
   long long want = (512 + tiles - 1) / tiles;

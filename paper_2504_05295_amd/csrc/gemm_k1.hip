@@ -2,6 +2,6 @@
 #include "gemm_dispatch.hpp"
 namespace dion {
 hipError_t gemm_k1(int variant, bool bf16, bool gbf16, GemmArgs g, int batch, hipStream_t s) {
-  DION_DISPATCH_TYPES(SRC_SUM_KC, SRC_F32_KS, EPI_STORE, false)
+  return dispatch_types<CfgBig, CfgSmall, PRODUCT_VARIANTS, SRC_SUM_KC, SRC_F32_KS, EPI_STORE, false>(variant, bf16, gbf16, g, batch, s);
 }
 }  // namespace dion

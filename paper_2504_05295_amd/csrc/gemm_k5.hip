@@ -3,13 +3,6 @@
 #include "gemm_dispatch.hpp"
 namespace dion {
 hipError_t gemm_k5(int variant, bool bf16, bool gbf16, GemmArgs g, int batch, hipStream_t s) {
-#define DION_K5(BF16, GBF16) \
-  { DION_DISPATCH_TILES(CfgUpdate, CfgSmall, BF16, SRC_F32_KC, SRC_F32_KC, GBF16, EPI_UPDATE, true) }
-  if (bf16) {
-    if (gbf16) DION_K5(true, true) else DION_K5(true, false)
-  } else {
-    if (gbf16) DION_K5(false, true) else DION_K5(false, false)
-  }
-#undef DION_K5
+  return dispatch_types<CfgUpdate, CfgSmall, UPDATE_VARIANTS, SRC_F32_KC, SRC_F32_KC, EPI_UPDATE, true>(variant, bf16, gbf16, g, batch, s);
 }
 }  // namespace dion

@@ -18,8 +18,11 @@
 #include "../../include/dion.h"
 #include "../../paper_2504_05295_amd/csrc/inv_tree_order.hpp"
 
-// (dion_api.hip; variant 0 and 3 are the 128 x 128 tiles, 1 and 4 the 64 x 64 ones, internal.hpp)
+// (dion_api.hip; the variants, as internal.hpp numbers them: 0 and 3 the large tiles, 1 and 4 those of 64 x 64, exact and
+// ragged; 5 fewer columns than a tile, 2 any size)
 namespace dion {
+int pick_variant(long long M, long long N, long long K, long long batch, bool aligned);
+int pick_update_variant(long long M, long long N, long long K, long long batch);
 int product_variant(long long M, long long N, long long K, long long batch, long long split);
 }
 
@@ -102,6 +105,32 @@ int main() {
         for (long long split : {1, 2, 16}) {
           const int v = dion::product_variant(m, r, m, batch, split);
           EXPECT((v != 0 && v != 3) || (m + 127) / 128 * ((r + 127) / 128) * batch * split >= 256);
+        }
+  // every product is given a variant that is compiled for it and that its sizes allow
+  const long long sizes[] = {1, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 191, 192, 256, 320, 1000, 4096, 8192};
+  for (long long m : sizes)
+    for (long long n : sizes)
+      for (long long r : sizes)
+        for (long long batch : {1, 5, 300}) {
+          if (r > m || r > n) continue;
+          auto fits = [&](int v, long long M, long long N, long long K, long long bm, long long bn, long long bk) {
+            if (v == 0) return M % bm == 0 && N % bn == 0 && K % bk == 0;
+            if (v == 1) return M % 64 == 0 && N % 64 == 0 && K % 64 == 0;
+            if (v == 3) return M >= bm && N >= bn && K >= bk;
+            if (v == 4) return M >= 64 && N >= 64 && K >= 64;
+            return v == 2;
+          };
+          EXPECT(fits(dion::pick_update_variant(m, n, r, batch), m, n, r, 128, 64, 32));
+          int v = dion::pick_variant(r, r, m, batch, true);
+          EXPECT(v != 3 && fits(v, r, r, m, 128, 128, 32));
+          v = dion::pick_variant(m, r, r, batch, true);
+          EXPECT(v != 3 && fits(v, m, r, r, 128, 128, 32));
+          for (long long split : {1, 4, 16}) {
+            v = dion::product_variant(m, r, n, batch, split);
+            EXPECT(v == 5 ? m >= 64 && n >= 64 && r < 64 : fits(v, m, r, n, 128, 128, 32));
+          }
+          v = dion::pick_variant(64 * m, 64 * r, 64 * r, batch, true);
+          EXPECT(v == 0 || v == 1);
         }
   // tile order of the triangular inverse
   size_t orders = 0;
