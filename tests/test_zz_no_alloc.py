@@ -43,6 +43,32 @@ def test_static_workspace_step_matches_dion_step():
             assert same          # the same kernels in the same order on the same inputs: nothing to differ by
 
 
+def test_static_workspace_with_and_without_split_products():
+    # The first shape needs more than the static workspace with its partial results and runs unsplit; the second fits with
+    # them.  In turn, so that each plan is made over what the other has left.
+    import torch
+    from paper_2504_05295_amd import binding as B
+    shapes = [(1536, 1536, 256), (1000, 700, 100)]
+    need = [B.dion_workspace_bytes([s], B.DION_G_F32, B.DION_MATH_F32) for s in shapes]
+    assert need[0] > B.DION_STATIC_SCRATCH_BYTES >= need[1]
+    status = torch.full((1,), 77, dtype=torch.int32, device="cuda")
+    refs = [GpuProblem([s], False, "f32") for s in shapes]
+    own = [[t[0].clone() for t in (p.X, p.M, p.Q)] for p in refs]
+    for t in range(2):
+        for shape, ref, (X, M, Q) in zip(shapes, refs, own):
+            ref.upload_grads(ref.grads_np(t))
+            assert ref.step(MU, ETA) == (0, -1)
+            B.dion_step_static(X, ref.G[0], M, Q, B.DION_G_F32, B.DION_MATH_F32, MU, ETA, status=status)
+            torch.cuda.synchronize()
+            assert int(status.item()) == 0
+            err = [relf(u.cpu().numpy(), v[0].cpu().numpy()) for u, v in zip((X, M, Q), (ref.X, ref.M, ref.Q))]
+            print(shape, "step", t, "rel err X %.1e M %.1e Q %.1e" % tuple(err), flush=True)
+            if shape == shapes[0]:
+                assert 0 < max(err) <= 1e-5      # the same sums of 1536 fp32 products in another order
+            else:
+                assert max(err) == 0.0
+
+
 def test_static_workspace_rejects_what_does_not_fit():
     import torch
     from paper_2504_05295_amd import binding as B
