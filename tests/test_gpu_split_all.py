@@ -4,6 +4,9 @@ import pytest
 
 from paper_2504_05295_amd import inputs
 from gpu_harness import GpuProblem, one_step_report
+from test_gpu_double import run as run_double
+from test_gpu_lazy import run_lazy
+from test_gpu_transposed import T, run as run_transposed
 
 pytestmark = pytest.mark.gpu
 MU, ETA = inputs.MU, inputs.ETA
@@ -21,3 +24,18 @@ def test_two_steps(shape):
         # the bounds of the fixed-shape parity tests in this mode
         assert rep["X"] <= 2e-2 and rep["M"] <= 2e-2 and rep["dX"] <= 4e-2 and rep["dM"] <= 4e-2, (shape, t, rep)
         assert rep["orth"] <= 1e-3, (shape, t, rep)
+
+
+# the other steps on the same route, the bounds being those of their own tests on the direct-load path
+def test_lazy_with_and_without_a_refresh():
+    run_lazy([(4096, 4352, 1024)], True, "bf16", 2, 2, 2e-2, 2e-4, method="lapack")
+
+
+def test_transposed_form():
+    run_transposed([(4352, 4096, 1024)], [T], True, "bf16", 2, 2e-2, method="lapack")
+
+
+@pytest.mark.parametrize("warm", [True, False])
+def test_double_dion(warm):
+    # (from an empty buffer the second stage is badly conditioned while it fills up: the wider bound of the test at 8192 x 8192)
+    run_double([(4096, 4352)], 256, 1024, True, "bf16", 2, 2e-2, method="lapack", warm=warm, dx_tol=None if warm else 0.15)
