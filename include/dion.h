@@ -20,7 +20,7 @@
  * take it as an operand: in DION_MATH_F32, and in DION_MATH_BF16 for shapes whose outputs cannot fill the GPU with
  * 256 x 256 tiles, the sum is formed in registers on the way into the matrix cores; for the large shapes of
  * DION_MATH_BF16 (m, n multiples of 256, r a multiple of 256, at least 128 output tiles of 256 x 256 per group of
- * equal shapes) one pass first stores bf16(M + G) in the workspace, once and row-major (2 bytes per element), and
+ * equal shapes, or 64 for a single matrix with m, n of 4096 at least; m n below 2^31) one pass first stores bf16(M + G) in the workspace, once and row-major (2 bytes per element), and
  * both products read that copy (the product with (M + G)^T transposes it on the way from LDS into the registers).
  *
  * Conventions
@@ -44,7 +44,7 @@
  *   - No function throws.  The only process-wide data are per-device caches of "this kernel may use more than
  *     64 KB of LDS" (set once per device and kernel).  One dion_state_t must not be used from two threads at once,
  *     and steps sharing a state must run on one stream.
- *   - Ranks of 256 and more (up to 128 matrices per group of equal shapes) are factored by single-launch kernels
+ *   - Ranks of 193 and more (up to 128 matrices per group of equal shapes) are factored by single-launch kernels
  *     whose workgroups wait for one another and therefore must all be resident at once: one per compute unit,
  *     sized from the device's compute-unit count read at dion_init_state.  Steps of two states that run
  *     concurrently on two streams, or any other kernels that occupy compute units for long, can keep them from

@@ -113,8 +113,8 @@ struct Group {
   size_t ws_off;   // offset of the group's first matrix in the workspace (set by dion_init_state)
 };
 
-constexpr int kEventsPerGroup = 2 * DION_STAGE_COUNT;
-constexpr int K1_PARTS = 4;   // parts of the contraction of K1 when the bf16 copy of M + G is made alongside it   // a start and an end event per stage
+constexpr int kEventsPerGroup = 2 * DION_STAGE_COUNT;   // a start and an end event per stage
+constexpr int K1_PARTS = 4;   // parts of the contraction of K1 when the bf16 copy of M + G is made alongside it
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -181,10 +181,20 @@ void plan_gram(Group& g, bool lean) {
   if (g.m % 256 == 0 && g.n % 256 == 0 && g.r % 128 == 0) {
     const long long tiles = std::min(g.m, g.n) / 128 * (g.r / 128) * g.count;
     // 256 x 256 tiles: for half the compute units at least or, for a single matrix, whose tiles the direct-load core splits
-    // over the contraction, for a quarter of them with a contraction that gives each of four parts 16 slabs.
+    // over the contraction, for a quarter of them with a contraction that gives each of four parts 16 slabs (one product of
+    // an oblong matrix may then have 129 to 255 tiles, which are not split, and still gains).
     // At 8192 x 8192 r = 512 (64 tiles) the two products take 83 and 69 us, 14 us each to add up, and the copy 96 us, against 189 and
-    // 113 us with M + G formed in the loads of 128 x 128 tiles: 845 -> 824 us a step; Double Dion at 4096 x 4096 r = 256 / 1024:
-    // 1490 -> 1461.  (Below 64 tiles neither the split nor the copy pays; a batch's last round is not split.)
+    // 113 us with M + G formed in the loads of 128 x 128 tiles.  us a step, 128 x 128 tiles / direct-load core:
+    //   tiles of the two products       square                                      1 : 2.5
+    //    64 /  64,  64 / 160            4096 r = 1024  694 / 684                    4096 x 10240 r = 1024  1074 / 987
+    //                                   8192 r = 512   865 / 838                    8192 x 20480 r = 512   1716 / 1599
+    //                                   16384 r = 256  1922-1972 / 1949             16384 x 40960 r = 256  4586 / 4491
+    //    80 /  80,  80 / 200            5120 r = 1024  931 / 836                    5120 x 12800 r = 1024  1460 / 1231
+    //    96 /  96,  96 / 240            6144 r = 1024  1065 / 982                   6144 x 15360 r = 1024  1770 / 1557
+    //   112 / 112, 112 / 280            7168 r = 1024  1283 / 1143                  7168 x 17920 r = 1024  2395 / 2022
+    // and tall ones, Lazy-Dion with a refresh and the transposed form alike (4 to 21 per cent).  Below 64 it is mixed: at 32
+    // tiles the core loses (4096 r = 512 398 / 476, 8192 r = 256 639 / 666), at 48 from 2 per cent lost (4096 r = 768
+    // 580 / 591) to 15 gained (6144 x 15360 r = 512 1185 / 1030).  A batch's last round is not split.
     const long long tiles256 = g.r % 256 == 0 ? (std::min(g.m, g.n) / 256) * (g.r / 256) * g.count : 0;
     const bool big_tiles = tiles256 >= 128 || (g.count == 1 && tiles256 >= 64 && std::min(g.m, g.n) >= 4096);
     g.direct12 = big_tiles && g.m * g.n * 2 < (1ll << 32);
@@ -230,8 +240,8 @@ Carve carve_entry(const Group& g) {
   take(SLOT_WL16, b * (((size_t)g.r * g.r + 1) / 2));
   take(SLOT_EPART, GRAM_DEFECT_PARTS);
   take(SLOT_FAST, 1);
-  // split-k partial results of K1 / K2: of the general core, or whole partial matrices off the direct-load path; on it (one matrix only) the
-  // partial 256 x 256 tiles of a split last round, at most 256 of them
+  // split-k partial results of K1 / K2: of the general core, or whole partial matrices off the direct-load path; on it (one
+  // matrix only) the partial 256 x 256 tiles of a split last or only round, at most 256 of them
   auto parts = [](const ProductPlan& p, size_t out) { return p.splitk > 1 ? p.splitk * align_up(out, 4) : 0; };
   take(SLOT_KPART, !g.big ? std::max(parts(g.k1, mr), parts(g.k2, nr)) : g.k12_splitk > 1 ? (size_t)g.k12_splitk * std::max(mr, nr) : (g.direct12 && g.count == 1) ? (size_t)256 * 256 * 256 : 0);
   take(SLOT_SYNC, 2 * (size_t)sync_words(g.rp / CHOL_NB));
@@ -861,7 +871,7 @@ bool k1_in_parts(const RowCtx& c) {
   // after the first reads and rewrites the m x r result and ramps up and down once more (about 50 us).  At r = 4096
   // the two balance (7.26 against 7.33 ms); with short contractions (8192 x 8192, or the 196 matrices of the 3B
   // model) the parts cost far more than they hide.
-  // (Judged per matrix, whatever the batch: a matrix is then stepped with the same arithmetic alone and in a batch.)
+  // (Judged per matrix, whatever the batch.)
   const double hidden = 0.35 * (8.0 * (double)g.m * (double)g.n / 5.2e12);
   const double extra = (K1_PARTS - 1) * (8.0 * (double)g.m * (double)g.r / 5.0e12 + 50e-6);
   return hidden > 1.25 * extra;
@@ -1069,10 +1079,15 @@ int stage_orth_plain(const RowCtx& c, long long rows, const GramPlan& gp, int sl
   if (rank_tol > 0.f) {
     // Three passes.  Every column's pivot is measured against that column's own squared norm; columns that the first
     // pass drops come out exactly zero, meet a zero threshold and a zero pivot in the later passes, and are dropped
-    // again (the adaptive last pass measures them against zero, so that it can be skipped when the others are
-    // orthonormal: 4096 x 4096 r = 1024 saves a factorisation, 229 us, and a triangular product on every step).  The columns that stay can be badly conditioned among themselves (condition numbers of a few thousand
-    // while the buffer is still filling up), which is more than two passes repair: the second pass brings the
-    // first one's result to within the reach of the third, whose pivots are checked as usual.
+    // again.  The adaptive last pass measures them against zero, so that it can be skipped when the others are orthonormal
+    // to 1e-3, the rule of the plain step: 4096 x 4096 r = 1024 saves a factorisation, 229 us, and a triangular product on
+    // every step.  (In bf16 mode the skipped pass leaves ||P^T P - I||_F at 4e-5 to 1.1e-4 where it used to be 3e-5 to 7e-5,
+    // six steps from an empty buffer at 2048 x 2048 r = 512 and 4096 x 4096 r = 1024; the errors of the update, of
+    // M's change and of the factor against 64 bits, up to 6e-2, 2e-2 and 5e-2 while the buffer fills up, are the bf16
+    // operands' and the same to two digits wherever both kept the same columns.)  The columns that stay can be badly
+    // conditioned among themselves (condition numbers of a few thousand while the buffer is still filling up), which is
+    // more than two passes repair: the second pass brings the first one's result to within the reach of the third, whose
+    // pivots are checked as usual.
     const int mid = in_place ? slot_final : slot_a;
     rc = cholqr_pass(st, g, c.row0, c.batch, rows, gp, slot_a, slot_b, 0.f, 3.0e38f, c.big, false, 0.f, 1, c.s, rank_tol);
     if (rc != DION_OK) return rc;
@@ -1335,7 +1350,9 @@ void create_group_streams(dion_state* st) {
 // overlap) group gi goes to the caller's stream or one of the state's in turn; these start behind what the caller's stream
 // holds so far, and it goes on behind them, whether or not a group failed to enqueue.  Nothing but the pointer table and the
 // step counter, written before this, is shared between groups.  Two layers of d = 768, r = 192 (three groups of about 200 us
-// each, nearly all of it launches and kernels of a few workgroups): 617 us one after the other, 391 us so.
+// each, nearly all of it launches and kernels of a few workgroups): 616 us one after the other, 386 us so, when steps follow one
+// another and the host is a step ahead; a step that finds the queue empty, where a group's launches start only when the host has
+// enqueued the groups before it, 666 and 457-510 us.
 template <class F>
 int for_each_group(dion_state* st, hipStream_t s, F&& fn) {
   const int ng = (int)st->groups.size();

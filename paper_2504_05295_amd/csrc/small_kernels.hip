@@ -293,9 +293,10 @@ __global__ void __launch_bounds__(256) colnorm_partial_kernel(void* const* table
   if (ry == 0 && col < r) part[(long long)chunk * r + col] = (red[0][cx] + red[1][cx]) + (red[2][cx] + red[3][cx]);
 }
 // The same on a matrix that still is nsplit partial results `stride` floats apart in slot_part: adds them up in the order of
-// the splits, stores the sum to slot_out and takes its squares on the way, which saves a launch and a pass over the matrix
-// (5 us; a step at 1111 x 1733 r = 139 takes 200).  1024 threads, eight rows and two splits in flight each: 42 blocks of
-// 256 threads, as above, would leave the loads of eight splits one latency after the other.
+// the splits, stores the sum to slot_out and takes its squares on the way, which saves a launch and a pass over the matrix:
+// 2-3 us a product (256 x 256 r = 64: 78.0 -> 75.2 us a step, 2048 x 2048 r = 512: 2-3 us, 1111 x 1733 r = 139: 1 of 193).
+// 1024 threads, eight rows and two splits in flight each: 42 blocks of 256 threads, as above, would leave the loads of
+// eight splits one latency after the other.
 __global__ void __launch_bounds__(1024) colnorm_sum_partial_kernel(void* const* table, int nslots, int slot_part, int slot_out, long long rows,
                                                                    int r, int nsplit, long long stride) {
   const float* in = (const float*)table[(size_t)blockIdx.z * nslots + slot_part];
