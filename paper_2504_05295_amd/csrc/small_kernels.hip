@@ -1,4 +1,6 @@
 // Element-wise, reduction and panel kernels of the Dion step (everything that is not a tiled GEMM).
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace dion {
@@ -266,17 +268,20 @@ hipError_t launch_sum_partials(void* const* table, int nslots, int batch, int sl
 }
 
 // ---------------------------------------------------------------- ColNorm (update rule: V_new <- ColNorm(W))
+// (Blocks of rows lie on the grid's second axis, which ends at 65536: with more of them there are several launches, and
+// block_first is the first block of one.)
+constexpr int GRID_Y_MAX = 65535;
 // Stage 1: partial[chunk][col] = sum over the chunk's COLNORM_ROWS rows of in[row][col]^2.  A pass over a matrix that is
 // usually still in a cache, so what bounds it is the latency of a thread's loads: eight are in flight per thread, added up
 // in a fixed order (256 x 64: 14.4 us with one load after the other, 3 us so).
-__global__ void __launch_bounds__(256) colnorm_partial_kernel(void* const* table, int nslots, int slot_in, long long rows, int r) {
+__global__ void __launch_bounds__(256) colnorm_partial_kernel(void* const* table, int nslots, int slot_in, long long rows, int r,
+                                                              int block_first) {
   const float* in = (const float*)table[(size_t)blockIdx.z * nslots + slot_in];
   float* part = (float*)table[(size_t)blockIdx.z * nslots + SLOT_SPART];
   __shared__ float red[4][64];
   const int cx = threadIdx.x & 63, ry = threadIdx.x >> 6;
-  const int ncb = (r + 63) / 64, chunk = blockIdx.x / ncb;
-  const int col = blockIdx.x % ncb * 64 + cx;
-  const long long row_begin = (long long)chunk * COLNORM_ROWS;
+  const int col = blockIdx.x * 64 + cx;
+  const long long row_begin = (long long)(block_first + (int)blockIdx.y) * COLNORM_ROWS;
   const int nrows = (int)min((long long)COLNORM_ROWS, rows - row_begin);
   float acc = 0.f;
   if (col < r) {
@@ -290,7 +295,7 @@ __global__ void __launch_bounds__(256) colnorm_partial_kernel(void* const* table
   }
   red[ry][cx] = acc;
   __syncthreads();
-  if (ry == 0 && col < r) part[(long long)chunk * r + col] = (red[0][cx] + red[1][cx]) + (red[2][cx] + red[3][cx]);
+  if (ry == 0 && col < r) part[(long long)(block_first + (int)blockIdx.y) * r + col] = (red[0][cx] + red[1][cx]) + (red[2][cx] + red[3][cx]);
 }
 // The same on a matrix that still is nsplit partial results `stride` floats apart in slot_part: adds them up in the order of
 // the splits, stores the sum to slot_out and takes its squares on the way, which saves a launch and a pass over the matrix:
@@ -298,15 +303,14 @@ __global__ void __launch_bounds__(256) colnorm_partial_kernel(void* const* table
 // 1024 threads, eight rows and two splits in flight each: 42 blocks of 256 threads, as above, would leave the loads of
 // eight splits one latency after the other.
 __global__ void __launch_bounds__(1024) colnorm_sum_partial_kernel(void* const* table, int nslots, int slot_part, int slot_out, long long rows,
-                                                                   int r, int nsplit, long long stride) {
+                                                                   int r, int nsplit, long long stride, int block_first) {
   const float* in = (const float*)table[(size_t)blockIdx.z * nslots + slot_part];
   float* out = (float*)table[(size_t)blockIdx.z * nslots + slot_out];
   float* part = (float*)table[(size_t)blockIdx.z * nslots + SLOT_SPART];
   __shared__ float red[16][64];
   const int cx = threadIdx.x & 63, ry = threadIdx.x >> 6;
-  const int ncb = (r + 63) / 64, chunk = blockIdx.x / ncb;
-  const int col = blockIdx.x % ncb * 64 + cx;
-  const long long row_begin = (long long)chunk * COLNORM_ROWS;
+  const int col = blockIdx.x * 64 + cx;
+  const long long row_begin = (long long)(block_first + (int)blockIdx.y) * COLNORM_ROWS;
   const int nrows = (int)min((long long)COLNORM_ROWS, rows - row_begin);
   float acc = 0.f;
   if (col < r) {
@@ -335,7 +339,7 @@ __global__ void __launch_bounds__(1024) colnorm_sum_partial_kernel(void* const* 
     float sum = 0.f;
 #pragma unroll
     for (int u = 0; u < 16; u += 4) sum += (red[u][cx] + red[u + 1][cx]) + (red[u + 2][cx] + red[u + 3][cx]);
-    part[(long long)chunk * r + col] = sum;
+    part[(long long)(block_first + (int)blockIdx.y) * r + col] = sum;
   }
 }
 static_assert(COLNORM_ROWS == 128, "colnorm_sum_partial_kernel: sixteen rows at a time, eight times");
@@ -380,14 +384,16 @@ hipError_t launch_colnorm_final(void* const* table, int nslots, int batch, int n
 hipError_t launch_colnorm(void* const* table, int nslots, int batch, int slot_in, long long rows, int r, hipStream_t s, int* pending,
                           PendingSum sum) {
   const int nchunks = (int)((rows + COLNORM_ROWS - 1) / COLNORM_ROWS);
-  const unsigned blocks = (unsigned)nchunks * ((r + 63) / 64);   // (on one axis: the others end at 65536)
-  if (sum.nsplit > 1)
-    hipLaunchKernelGGL(colnorm_sum_partial_kernel, dim3(blocks, 1, batch), dim3(1024), 0, s, table, nslots, SLOT_KPART, slot_in,
-                       rows, r, sum.nsplit, sum.stride);
-  else
-    hipLaunchKernelGGL(colnorm_partial_kernel, dim3(blocks, 1, batch), dim3(256), 0, s, table, nslots, slot_in, rows, r);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  for (int first = 0; first < nchunks; first += GRID_Y_MAX) {
+    const dim3 grid((r + 63) / 64, std::min(nchunks - first, GRID_Y_MAX), batch);
+    if (sum.nsplit > 1)
+      hipLaunchKernelGGL(colnorm_sum_partial_kernel, grid, dim3(1024), 0, s, table, nslots, SLOT_KPART, slot_in, rows, r, sum.nsplit,
+                         sum.stride, first);
+    else
+      hipLaunchKernelGGL(colnorm_partial_kernel, grid, dim3(256), 0, s, table, nslots, slot_in, rows, r, first);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   return launch_colnorm_final(table, nslots, batch, nchunks, r, s, pending);
 }
 
@@ -397,19 +403,17 @@ hipError_t launch_colnorm(void* const* table, int nslots, int batch, int slot_in
 // columns (in the same order, so all take the same d), and the first one of a column block leaves s and d in memory.
 __global__ void __launch_bounds__(256) scale_cols_kernel(void* const* table, int nslots, int slot_in, int slot_out, long long rows,
                                                          int r, int status_slot, int slot_out16, int slot_in16, int null_slot,
-                                                         int nchunks) {
+                                                         int nchunks, int block_first) {
   void* const* tab = table + (size_t)blockIdx.z * nslots;
   __shared__ float dsh[256];
-  const int ncb = (r + 255) / 256, cb = blockIdx.x % ncb;
-  const long long rb = blockIdx.x / ncb;
   if (nchunks > 0) {
     const float* part = (const float*)tab[SLOT_SPART];
-    const int c = cb * 256 + threadIdx.x;
+    const int c = blockIdx.x * 256 + threadIdx.x;
     if (c < r) {
       const float nrm = sqrtf(sum_planes<float>(part + c, r, nchunks));
       const float dv = 1.0f / (nrm + COLNORM_EPS);
       dsh[threadIdx.x] = dv;
-      if (rb == 0) {
+      if (block_first + (int)blockIdx.y == 0) {
         ((float*)tab[SLOT_S])[c] = nrm;
         ((float*)tab[SLOT_D])[c] = dv;
       }
@@ -424,9 +428,9 @@ __global__ void __launch_bounds__(256) scale_cols_kernel(void* const* table, int
   const float* d = (const float*)tab[SLOT_D];
   const int* nullmask = null_slot >= 0 ? (const int*)tab[null_slot] : nullptr;
   // a block covers 32 rows x 256 columns; a thread owns 4 consecutive columns (or fewer at a ragged edge)
-  const int col = cb * 256 + (threadIdx.x & 63) * 4;
+  const int col = blockIdx.x * 256 + (threadIdx.x & 63) * 4;
   if (col >= r) return;
-  const long long row_end = min(rows, (rb + 1) * 32);
+  const long long row_begin = (long long)(block_first + (int)blockIdx.y) * 32, row_end = min(rows, row_begin + 32);
   // this thread's four factors (two separate reads: one pointer to either memory would be a generic one, and an offset
   // taken from it before the column index is added leaves the LDS aperture)
   f32x4_t dv = {0.f, 0.f, 0.f, 0.f};
@@ -450,7 +454,7 @@ __global__ void __launch_bounds__(256) scale_cols_kernel(void* const* table, int
     for (int e = 0; e < 4; ++e)
       if (e < ncol) { keep_old[e] = nullmask[col + e] != 0; any_old = any_old || keep_old[e]; }
   }
-  for (long long row0 = rb * 32 + (threadIdx.x >> 6); row0 < row_end; row0 += 32) {
+  for (long long row0 = row_begin + (threadIdx.x >> 6); row0 < row_end; row0 += 32) {
     f32x4_t v[8], o[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
@@ -499,11 +503,14 @@ __global__ void __launch_bounds__(256) scale_cols_kernel(void* const* table, int
 }
 hipError_t launch_scale_cols(void* const* table, int nslots, int batch, int slot_in, int slot_out, long long rows, int r,
                              int status_slot, int slot_out16, int slot_in16, hipStream_t s, int null_slot, int nchunks) {
-  // (row and column blocks on one axis: the others end at 65536, which is 2097152 rows)
-  const unsigned blocks = (unsigned)((rows + 31) / 32) * ((r + 255) / 256);
-  hipLaunchKernelGGL(scale_cols_kernel, dim3(blocks, 1, batch), dim3(256), 0, s, table, nslots,
-                     slot_in, slot_out, rows, r, status_slot, slot_out16, slot_in16, null_slot, nchunks);
-  return hipGetLastError();
+  const long long blocks = (rows + 31) / 32;
+  for (long long first = 0; first < blocks; first += GRID_Y_MAX) {
+    hipLaunchKernelGGL(scale_cols_kernel, dim3((r + 255) / 256, (unsigned)std::min<long long>(blocks - first, GRID_Y_MAX), batch), dim3(256), 0, s,
+                       table, nslots, slot_in, slot_out, rows, r, status_slot, slot_out16, slot_in16, null_slot, nchunks, (int)first);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // fp32 [rows][cols] -> bf16 [rows][cols] and / or bf16 [cols][rows], 64x64 tiles transposed through LDS.
