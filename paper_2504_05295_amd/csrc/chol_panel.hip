@@ -13,35 +13,13 @@
 // the two panel blocks L21_i and L21_j it needs with fp32 MFMA, and updates its tile.  The workgroups
 // of column j = 1 also store their L21_i into L.
 //
-// Inside a workgroup the diagonal block is the latency-critical part, so it is spread over the waves:
-//   wave 0  eliminates C11 column by column on unscaled values (row i of the block lives in the registers
-//           of lane i); it carries the chain of dependent pivots and does nothing that is not on it,
-//   wave 2  follows and scales the raw columns into columns of L11 (reciprocal square roots, bounds check),
-//   wave 1  follows wave 0 as well and builds W11 = L11^-1 by forward substitution on the raw columns,
-//   wave 3  meanwhile fetches the two panel blocks C21_i, C21_j into LDS.
-// The waves talk through LDS: broadcast reads (all lanes read one address) replace cross-lane shuffles, and
-// counters tell the followers which columns are final.  LDS operations of one wave are processed in issue
-// order, so data stored before a counter is visible to whoever sees the counter.
-#include <type_traits>
-#include <utility>
-
-#include "internal.hpp"
+// Inside a workgroup the diagonal block is the latency-critical part: three waves share it (chol_block.hpp), wave 3
+// meanwhile fetches the two panel blocks C21_i, C21_j into LDS.
+#include "chol_block.hpp"
 
 namespace dion {
 
 namespace {
-// compile-time loop: the body sees its index as a constant, so register arrays are indexed statically
-template <int B, int... Is, class F>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, Is...>, F&& f) {
-  (f(std::integral_constant<int, B + Is>{}), ...);
-}
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) static_for_impl<B>(std::make_integer_sequence<int, E - B>{}, f);
-}
-constexpr int CB = CHOL_NB;   // 64
-constexpr int CBP = CB + 4;   // LDS row stride (floats): conflict-free 16-byte reads
-
 // acc = As[64 x 64] * Bs[64 x 64]^T for this wave's 32x32 quadrant (LDS tiles, k contiguous).
 __device__ __forceinline__ f32x16_t mma_64(const float* As, const float* Bs, int wm, int wn, int lr, int lk) {
   f32x16_t acc;
@@ -57,214 +35,6 @@ __device__ __forceinline__ f32x16_t mma_64(const float* As, const float* Bs, int
   return acc;
 }
 }  // namespace
-
-// LDS pointers carry their address space, so that volatile accesses too become ds_* instructions (a volatile
-// access through a generic pointer is a flat one, with a much longer round trip).
-typedef __attribute__((address_space(3))) float lds_float;
-typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
-typedef __attribute__((address_space(3))) volatile int lds_counter;
-
-__device__ __forceinline__ float lane_value(float x, int src_lane) {   // x of lane `src_lane`, uniform result
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), src_lane));
-}
-
-// Wave 0: eliminates the 64x64 block held in S0 (row i in lane i), right-looking, one column per step,
-// working on raw (unscaled) values: with g = a[i][j] / a[j][j] the update is a[i][k] -= g * a[k][j], which
-// equals L[i][j] L[k][j].  The dependency chain from one pivot to the next is kept free of LDS round trips:
-// the pivot and the two entries of the column that the next two columns need come through lane reads, and
-// column j's update of the entries further right (k >= j+3) is applied one step late, from the copy of the
-// raw column that went through LDS meanwhile.  Raw column j is left in row j of S0 (its first reader, this
-// wave, took the whole block into registers before the first column is written) and *raw_done counts them.
-// RANK (the factorisation that tolerates linearly dependent columns): a column whose pivot is not above its
-// threshold thr[j] (a fraction of the Gram matrix' original diagonal entry) is dependent on the columns before it; it
-// eliminates nothing, so that the factorisation goes on as if the column were not there.  The two follower waves
-// take the same decision from the same two numbers.
-template <bool RANK>
-__device__ __forceinline__ void eliminate_wave(lds_float* S0, lds_counter* raw_done, int lane, const float* thr) {
-    float a[CB];
-    float thr_lane = 0.f;
-    if constexpr (RANK) thr_lane = thr[lane];
-    static_for<0, CB>([&](auto kc) __attribute__((always_inline)) { a[decltype(kc)::value] = S0[lane * CBP + decltype(kc)::value]; });
-    f32x4_t cv0[CB / 4], cv1[CB / 4];   // raw columns j (even / odd) as read back from LDS
-    float gprev = 0.f;
-    static_for<0, CB>([&](auto jc) __attribute__((always_inline)) {
-      constexpr int jj = decltype(jc)::value;
-      f32x4_t* cur = (jj & 1) ? cv1 : cv0;
-      const f32x4_t* prev = (jj & 1) ? cv0 : cv1;
-      const float piv = lane_value(a[jj], jj);
-      float gj = a[jj] * __builtin_amdgcn_rcpf(piv);
-      if constexpr (RANK) {
-        if (!(piv > lane_value(thr_lane, jj))) gj = 0.f;   // uniform
-      }
-      if constexpr (jj + 1 < CB) a[jj + 1] -= gj * lane_value(a[jj], jj + 1);
-      if constexpr (jj + 2 < CB) {
-        if constexpr (jj >= 1) a[jj + 2] -= gprev * prev[(jj + 2) / 4][(jj + 2) % 4];
-        a[jj + 2] -= gj * lane_value(a[jj], jj + 2);
-      }
-      lds_float* cb = S0 + jj * CBP;
-      cb[lane] = a[jj];
-      if constexpr (jj + 3 < CB) {
-        // entries below j+3 of the first group of four are not read at all: their registers would be reused at
-        // once, and the hardware then waits for the read before it lets them be overwritten
-        constexpr int q0 = (jj + 3) / 4;
-        static_for<jj + 3, (4 * q0 + 4 < CB ? 4 * q0 + 4 : CB)>([&](auto kc) __attribute__((always_inline)) {
-          constexpr int k = decltype(kc)::value;
-          cur[q0][k % 4] = cb[k];
-        });
-        static_for<q0 + 1, CB / 4>([&](auto qc) __attribute__((always_inline)) {
-          constexpr int q = decltype(qc)::value;
-          cur[q] = *(const lds_f32x4*)(cb + 4 * q);
-        });
-      }
-      asm volatile("" ::: "memory");
-      *raw_done = jj + 1;
-      // the reads above stay in flight across the rest of this step; nothing below may move up past them
-      __builtin_amdgcn_sched_barrier(0);
-      // late part of column j-1's update
-      if constexpr (jj >= 1) {
-        static_for<(jj + 3) / 4, CB / 4>([&](auto qc) __attribute__((always_inline)) {
-          constexpr int q = decltype(qc)::value;
-          if constexpr (4 * q + 0 >= jj + 3) a[4 * q + 0] -= gprev * prev[q][0];
-          if constexpr (4 * q + 1 >= jj + 3) a[4 * q + 1] -= gprev * prev[q][1];
-          if constexpr (4 * q + 2 >= jj + 3) a[4 * q + 2] -= gprev * prev[q][2];
-          if constexpr (4 * q + 3 >= jj + 3) a[4 * q + 3] -= gprev * prev[q][3];
-        });
-      }
-      gprev = gj;
-      __builtin_amdgcn_sched_barrier(0);
-    });
-}
-
-// Wave 2: follows wave 0 and turns raw columns into columns of L: L[i][j] = raw[i][j] / sqrt(raw[j][j]).
-// Leaves 1 / sqrt(raw[j][j]) in rsv and sets *scaled when all of them are there.  When Lout is given
-// (writer workgroup) also stores L11 and the status.
-// RANK: a dependent column (pivot not above thr[j]) becomes a zero column of L with a zero diagonal entry and 0 in rsv,
-// which makes row and column j of the inverse zero as well; nullmask[j] (writer only) records the decision.
-template <bool RANK>
-__device__ __forceinline__ void scale_wave(const lds_float* S0, lds_counter* raw_done, lds_float* rsv, lds_counter* scaled, int lane,
-                                           float piv_lo, float piv_hi, float* Lout, long long ld, int* status, const float* thr,
-                                           int* nullmask) {
-    float l[CB];
-    bool bad = false;
-    int seen = 0;
-    float thr_lane = 0.f;       // (thresholds in a register, decisions in a mask: a load and a store to memory per column
-    unsigned long long null_cols = 0;   // made this wave, and with it the block, end 3 us late)
-    if constexpr (RANK) thr_lane = thr[lane];
-    float raw0 = 0.f, raw1 = 0.f, piv0 = 1.f, piv1 = 1.f;
-    // column j+1 is fetched while column j is being scaled; a column is only asked for once it is final
-    auto fetch = [&](auto jc, float& raw, float& piv) __attribute__((always_inline)) {
-      constexpr int jj = decltype(jc)::value;
-      if (seen <= jj) {
-        do { seen = *raw_done; } while (seen <= jj);   // wave 0 always gets there: it waits for nobody
-      }
-      asm volatile("" ::: "memory");
-      raw = S0[jj * CBP + lane];
-      piv = S0[jj * CBP + jj];
-    };
-    fetch(std::integral_constant<int, 0>{}, raw0, piv0);
-    static_for<0, CB>([&](auto jc) __attribute__((always_inline)) {
-      constexpr int jj = decltype(jc)::value;
-      const float raw = (jj & 1) ? raw1 : raw0, piv = (jj & 1) ? piv1 : piv0;
-      if constexpr (jj + 1 < CB) fetch(std::integral_constant<int, jj + 1>{}, (jj & 1) ? raw0 : raw1, (jj & 1) ? piv0 : piv1);
-      __builtin_amdgcn_sched_barrier(0);
-      float rs = __builtin_amdgcn_rsqf(piv);
-      rs = rs * (1.5f - 0.5f * piv * rs * rs);   // one Newton step on the hardware estimate
-      if constexpr (RANK) {
-        const bool dependent = !(piv > lane_value(thr_lane, jj));
-        if (dependent) rs = 0.f;
-        bad = bad || !(piv == piv) || (!dependent && (!(piv > piv_lo) || !(piv < piv_hi)));   // a NaN pivot is no dependent column
-        null_cols |= dependent ? 1ull << jj : 0ull;
-      } else {
-        bad = bad || !(piv > piv_lo) || !(piv < piv_hi);
-      }
-      l[jj] = raw * rs;
-      rsv[jj] = rs;   // every lane stores the same value
-      asm volatile("" : "+v"(l[jj]));   // keeps this column's arithmetic from being moved past the next wait loop
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    asm volatile("" ::: "memory");
-    *scaled = 1;
-    if constexpr (RANK) {
-      if (nullmask) nullmask[lane] = (int)((null_cols >> lane) & 1ull);
-    }
-    if (Lout) {
-      static_for<0, CB>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;
-        Lout[(long long)lane * ld + k] = (k <= lane) ? l[k] : 0.f;
-      });
-      if (bad && lane == 0 && *status == 0) *status = ST_BREAKDOWN;   // a code that is already there (an earlier stage failed) stays
-    }
-}
-
-// Wave 1: W11 = L11^-1, following wave 0 column by column; leaves W11 (row-major) in S0.
-// Lane c builds column c of W by forward substitution in its right-looking form, on raw values as well:
-// with acc_i = delta_ic - sum_{k<j} L[i][k] w_k, step j sets acc_i -= raw[i][j] * (acc_j / raw[j][j]) for i > j,
-// and w_j = acc_j / sqrt(raw[j][j]) is applied to all rows at the end.  The work per step shrinks as the
-// elimination's does, so this wave finishes right behind wave 0.
-template <bool RANK>
-__device__ __forceinline__ void invert_wave(lds_float* S0, lds_counter* raw_done, const lds_float* rsv, lds_counter* scaled, int lane,
-                                            const float* thr) {
-    float w[CB];
-    static_for<0, CB>([&](auto ic) __attribute__((always_inline)) { w[decltype(ic)::value] = (lane == decltype(ic)::value) ? 1.f : 0.f; });
-    f32x4_t cv0[CB / 4], cv1[CB / 4];
-    float piv0 = 1.f, piv1 = 1.f;
-    int seen = 0;
-    float thr_lane = 0.f;
-    if constexpr (RANK) thr_lane = thr[lane];
-    // raw column j+1 is fetched while column j is being used; a column is only asked for once it is final
-    auto fetch = [&](auto jc, f32x4_t* cv, float& piv) __attribute__((always_inline)) {
-      constexpr int jj = decltype(jc)::value;
-      if (seen <= jj) {
-        do { seen = *raw_done; } while (seen <= jj);   // wave 0 always gets there: it waits for nobody
-      }
-      asm volatile("" ::: "memory");
-      const lds_float* cb = S0 + jj * CBP;
-      piv = cb[jj];
-      if constexpr (jj + 1 < CB) {
-        constexpr int q0 = (jj + 1) / 4;   // entries up to j of the first group of four are not read (see wave 0)
-        static_for<jj + 1, (4 * q0 + 4 < CB ? 4 * q0 + 4 : CB)>([&](auto kc) __attribute__((always_inline)) {
-          constexpr int k = decltype(kc)::value;
-          cv[q0][k % 4] = cb[k];
-        });
-        static_for<q0 + 1, CB / 4>([&](auto qc) __attribute__((always_inline)) {
-          constexpr int q = decltype(qc)::value;
-          cv[q] = *(const lds_f32x4*)(cb + 4 * q);
-        });
-      }
-    };
-    fetch(std::integral_constant<int, 0>{}, cv0, piv0);
-    static_for<0, CB>([&](auto jc) __attribute__((always_inline)) {
-      constexpr int jj = decltype(jc)::value;
-      const f32x4_t* cv = (jj & 1) ? cv1 : cv0;
-      const float piv = (jj & 1) ? piv1 : piv0;
-      if constexpr (jj + 1 < CB) fetch(std::integral_constant<int, jj + 1>{}, (jj & 1) ? cv0 : cv1, (jj & 1) ? piv0 : piv1);
-      __builtin_amdgcn_sched_barrier(0);
-      float u = w[jj] * __builtin_amdgcn_rcpf(piv);
-      if constexpr (RANK) {
-        if (!(piv > lane_value(thr_lane, jj))) u = 0.f;   // a dependent column takes no part in the substitution
-      }
-      static_for<(jj + 1) / 4, CB / 4>([&](auto qc) __attribute__((always_inline)) {
-        constexpr int q = decltype(qc)::value;
-        if constexpr (4 * q + 0 > jj) w[4 * q + 0] -= cv[q][0] * u;
-        if constexpr (4 * q + 1 > jj) w[4 * q + 1] -= cv[q][1] * u;
-        if constexpr (4 * q + 2 > jj) w[4 * q + 2] -= cv[q][2] * u;
-        if constexpr (4 * q + 3 > jj) w[4 * q + 3] -= cv[q][3] * u;
-      });
-      // keeps this step's arithmetic from being moved past the next wait loop
-      static_for<jj + 1, CB>([&](auto kc) __attribute__((always_inline)) {
-        float& wk = w[decltype(kc)::value];
-        asm volatile("" : "+v"(wk));
-      });
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    while (*scaled == 0) __builtin_amdgcn_s_sleep(1);   // wave 2 always gets there: it waits only for wave 0
-    asm volatile("" ::: "memory");
-    // waves 0 and 2 are through with S0 by now
-    static_for<0, CB>([&](auto rc) __attribute__((always_inline)) {
-      constexpr int rr = decltype(rc)::value;
-      S0[rr * CBP + lane] = w[rr] * rsv[rr];
-    });
-}
 
 template <bool RANK>
 __global__ void __launch_bounds__(256, 2) chol_panel_kernel(CholPanelPtrs p, int k0, int rp, float piv_lo, float piv_hi, int mode) {
@@ -286,9 +56,7 @@ __global__ void __launch_bounds__(256, 2) chol_panel_kernel(CholPanelPtrs p, int
   __shared__ __attribute__((aligned(16))) float S0[CB * CBP];   // C11, later W11
   __shared__ __attribute__((aligned(16))) float S1[CB * CBP];   // C21_i, later L21_i
   __shared__ __attribute__((aligned(16))) float S2[CB * CBP];   // C21_j, later L21_j
-  __shared__ float rsv[CB];                                     // 1 / L[j][j]
-  __shared__ volatile int scaled;                               // set when rsv is complete
-  __shared__ volatile int raw_done;                             // number of eliminated (raw) columns
+  __shared__ volatile int sync[chol_block::COUNTERS];           // of the diagonal block's waves
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave & 1, wn = wave >> 1, lr = lane & 31, lk = lane >> 5;
 
@@ -315,7 +83,7 @@ __global__ void __launch_bounds__(256, 2) chol_panel_kernel(CholPanelPtrs p, int
     }
     *(f32x4_t*)(S0 + rr * CBP + cc) = v;
   }
-  if (t == 0) { scaled = 0; raw_done = 0; }
+  if (t < chol_block::COUNTERS) sync[t] = 0;
   // this thread's 16 entries of the trailing tile, fetched now so that they arrive during the factorisation
   float cold[16];
   if (!writer) {
@@ -333,13 +101,9 @@ __global__ void __launch_bounds__(256, 2) chol_panel_kernel(CholPanelPtrs p, int
       *(f32x4_t*)(S1 + rr * CBP + cc) = *(const f32x4_t*)(C + (rowi + rr) * ld + k0 + cc);
       if (j != i) *(f32x4_t*)(S2 + rr * CBP + cc) = *(const f32x4_t*)(C + (rowj + rr) * ld + k0 + cc);
     }
-  } else if (wave == 0) {
-    eliminate_wave<RANK>((lds_float*)S0, (lds_counter*)&raw_done, lane, thr);
-  } else if (wave == 2) {
-    scale_wave<RANK>((const lds_float*)S0, (lds_counter*)&raw_done, (lds_float*)rsv, (lds_counter*)&scaled, lane, piv_lo, piv_hi,
-                     writer ? L + (long long)k0 * ld + k0 : nullptr, ld, status, thr, writer ? nullmask : nullptr);
-  } else if (wave == 1) {
-    invert_wave<RANK>((lds_float*)S0, (lds_counter*)&raw_done, (const lds_float*)rsv, (lds_counter*)&scaled, lane, thr);
+  } else if (wave < 3) {
+    chol_block::factor_invert<RANK>(S0, (chol_block::lds_counter*)sync, wave, lane, piv_lo, piv_hi,
+                                    writer ? L + (long long)k0 * ld + k0 : nullptr, ld, status, RANK ? thr[lane] : 0.f, writer ? nullmask : nullptr);
   } else if (!writer) {
     for (int idx = lane; idx < CB * CB / 4; idx += 64) {
       const int rr = idx >> 4, cc = (idx & 15) * 4;
@@ -395,10 +159,8 @@ __global__ void __launch_bounds__(256, 1) chol_small_kernel(CholSmallArgs p) {
   if (p.skip && p.skip[mat] != 0) return;   // uniform
   constexpr int TILES = NB * (NB + 1) / 2;
   __shared__ __attribute__((aligned(16))) float T[TILES][CB * CBP];
-  __shared__ float rsv[CB];
   __shared__ float red[256];
-  __shared__ volatile int scaled;
-  __shared__ volatile int raw_done;
+  __shared__ volatile int sync[chol_block::COUNTERS];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave & 1, wn = wave >> 1, lr = lane & 31, lk = lane >> 5;
   const int frow = wm * 32 + 4 * lk, fcol = wn * 32 + lr;
@@ -506,16 +268,10 @@ __global__ void __launch_bounds__(256, 1) chol_small_kernel(CholSmallArgs p) {
 #pragma unroll 1   // (three copies of the diagonal block's code are more than the instruction cache holds)
   for (int k = 0; k < NB; ++k) {
     float* S0 = tile(k, k);
-    if (t == 0) { scaled = 0; raw_done = 0; }
+    if (t < chol_block::COUNTERS) sync[t] = 0;
     __syncthreads();
-    if (wave == 0) {
-      eliminate_wave<false>((lds_float*)S0, (lds_counter*)&raw_done, lane, nullptr);
-    } else if (wave == 2) {
-      scale_wave<false>((const lds_float*)S0, (lds_counter*)&raw_done, (lds_float*)rsv, (lds_counter*)&scaled, lane, p.piv_lo, p.piv_hi,
-                        L + (long long)k * CB * (ld + 1), ld, p.status + blockIdx.x, nullptr, nullptr);
-    } else if (wave == 1) {
-      invert_wave<false>((lds_float*)S0, (lds_counter*)&raw_done, (const lds_float*)rsv, (lds_counter*)&scaled, lane, nullptr);
-    }
+    chol_block::factor_invert<false>(S0, (chol_block::lds_counter*)sync, wave, lane, p.piv_lo, p.piv_hi, L + (long long)k * CB * (ld + 1), ld,
+                                     p.status + blockIdx.x, 0.f, nullptr);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -767,9 +523,7 @@ __global__ void __launch_bounds__(256, 1) chol_stream_kernel(CholStreamArgs p) {
   __shared__ __attribute__((aligned(16))) float S0[CB * CBP];   // diagonal block / W11
   __shared__ __attribute__((aligned(16))) float S1[CB * CBP];
   __shared__ __attribute__((aligned(16))) float S2[CB * CBP];
-  __shared__ float rsv[CB];
-  __shared__ volatile int scaled;
-  __shared__ volatile int raw_done;
+  __shared__ volatile int sync[chol_block::COUNTERS];
   __shared__ int gave_up;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave & 1, wn = wave >> 1, lr = lane & 31, lk = lane >> 5;
@@ -801,16 +555,11 @@ __global__ void __launch_bounds__(256, 1) chol_stream_kernel(CholStreamArgs p) {
         *(f32x4_t*)(S0 + rr * CBP + cc) = v;
       }
     }
-    if (t == 0) { scaled = 0; raw_done = 0; }
+    if (t < chol_block::COUNTERS) sync[t] = 0;
     __syncthreads();
-    if (wave == 0) {
-      eliminate_wave<RANK>((lds_float*)S0, (lds_counter*)&raw_done, lane, RANK ? thr + k * CB : nullptr);
-    } else if (wave == 2) {
-      scale_wave<RANK>((const lds_float*)S0, (lds_counter*)&raw_done, (lds_float*)rsv, (lds_counter*)&scaled, lane, x.piv_lo, x.piv_hi,
-                       (float*)(x.L + at), ld, x.status, RANK ? thr + k * CB : nullptr, RANK ? nullmask + k * CB : nullptr);
-    } else if (wave == 1) {
-      invert_wave<RANK>((lds_float*)S0, (lds_counter*)&raw_done, (const lds_float*)rsv, (lds_counter*)&scaled, lane,
-                        RANK ? thr + k * CB : nullptr);
+    if (wave < 3) {
+      chol_block::factor_invert<RANK>(S0, (chol_block::lds_counter*)sync, wave, lane, x.piv_lo, x.piv_hi, (float*)(x.L + at), ld, x.status,
+                                      RANK ? thr[k * CB + lane] : 0.f, RANK ? nullmask + k * CB : nullptr);
     } else if (pending_flag) {
 #pragma unroll 8
       for (int rr = 0; rr < CB; ++rr) shared_store(pending_tile + rr * ld + lane, S1[rr * CBP + lane]);
@@ -987,9 +736,7 @@ __global__ void __launch_bounds__(256, 1) chol_chain_kernel(CholStreamArgs p) {
   __shared__ __attribute__((aligned(16))) float S1[CB * CBP];
   __shared__ __attribute__((aligned(16))) float S2[CB * CBP];
   __shared__ __attribute__((aligned(16))) float S3[CB * CBP];
-  __shared__ float rsv[CB];
-  __shared__ volatile int scaled;
-  __shared__ volatile int raw_done;
+  __shared__ volatile int sync[chol_block::COUNTERS];
   __shared__ int gave_up;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave & 1, wn = wave >> 1, lr = lane & 31, lk = lane >> 5;
@@ -1012,9 +759,10 @@ __global__ void __launch_bounds__(256, 1) chol_chain_kernel(CholStreamArgs p) {
         if (cc + e > rr) v[e] = 0.f;
       *(f32x4_t*)(S0 + rr * CBP + cc) = v;
     }
+    float thr_next = RANK ? thr[lane] : 0.f;   // (of the next diagonal block: fetched a step ahead)
     for (int k = 0; k < nb; ++k) {
       const int at = (k * CB) * ld + k * CB;
-      if (t == 0) { scaled = 0; raw_done = 0; }
+      if (t < chol_block::COUNTERS) sync[t] = 0;
       __syncthreads();   // (also: everybody's stores of the last step, W11(k-1) and L[k][k-1], have completed)
 #ifdef DION_CHOL_TIMING
       if (t == 0 && p.dbg) p.dbg[8 * k + 0] = wall_clock64();
@@ -1023,14 +771,10 @@ __global__ void __launch_bounds__(256, 1) chol_chain_kernel(CholStreamArgs p) {
         flag_store(x.wflag + k - 1, x.epoch);           // W11(k-1) is out, and so is L[k][k-1]:
         flag_store(x.lflag + k, ep32 | (u64)k);         // the helper of the next look-ahead row fetches both at once
       }
-      if (wave == 0) {
-        eliminate_wave<RANK>((lds_float*)S0, (lds_counter*)&raw_done, lane, RANK ? thr + k * CB : nullptr);
-      } else if (wave == 2) {
-        scale_wave<RANK>((const lds_float*)S0, (lds_counter*)&raw_done, (lds_float*)rsv, (lds_counter*)&scaled, lane, x.piv_lo, x.piv_hi,
-                         (float*)(x.L + at), ld, x.status, RANK ? thr + k * CB : nullptr, RANK ? nullmask + k * CB : nullptr);
-      } else if (wave == 1) {
-        invert_wave<RANK>((lds_float*)S0, (lds_counter*)&raw_done, (const lds_float*)rsv, (lds_counter*)&scaled, lane,
-                          RANK ? thr + k * CB : nullptr);
+      if (wave < 3) {
+        chol_block::factor_invert<RANK>(S0, (chol_block::lds_counter*)sync, wave, lane, x.piv_lo, x.piv_hi, (float*)(x.L + at), ld, x.status,
+                                        thr_next, RANK ? nullmask + k * CB : nullptr);
+        if (RANK && k + 1 < nb) thr_next = thr[(k + 1) * CB + lane];
       } else if (k + 1 < nb) {
         // the idle wave: the two tiles of the next step in, once their owner has applied their last update
         bool ok = true;
