@@ -57,13 +57,13 @@ __device__ __forceinline__ float row_bcast(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + SRC, 0xf, 0xf, true));
 }
 // acc + Y X^T
-__device__ __forceinline__ f32x4_t mm(f32x4_t acc, const f32x4_t& Y, const f32x4_t& X) {
+__device__ __forceinline__ f32x4_t mm(f32x4_t acc, f32x4_t Y, f32x4_t X) {
 #pragma unroll
   for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[v], Y[v], acc, 0, 0, 0);
   return acc;
 }
 // the same on a dependent chain half as long
-__device__ __forceinline__ f32x4_t mm_short(f32x4_t acc, const f32x4_t& Y, const f32x4_t& X) {
+__device__ __forceinline__ f32x4_t mm_short(f32x4_t acc, f32x4_t Y, f32x4_t X) {
   f32x4_t b = {0.f, 0.f, 0.f, 0.f};
   acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[0], Y[0], acc, 0, 0, 0);
   b = __builtin_amdgcn_mfma_f32_16x16x4f32(X[1], Y[1], b, 0, 0, 0);

@@ -643,6 +643,7 @@ int cholqr_pass(dion_state* st, const Group& g, int row0, int batch, long long r
     ca.spin_limit = st->chol_spin_limit;
     ca.thr = pp.thr; ca.nullmask = pp.nullmask;
     ca.chain = chain;
+    ca.T = (float*)(st->ws + g.ws_off + (size_t)row0 * g.bytes_per_entry + g.carve.off[SLOT_T]);
     if (adaptive) {
       char* e0 = st->ws + g.ws_off + (size_t)row0 * g.bytes_per_entry;
       ca.skip = nullptr;   // (the flag is what this launch sets)
