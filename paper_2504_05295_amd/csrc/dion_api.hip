@@ -108,6 +108,8 @@ struct Group {
                       // 256 x 256 tiles (or, one matrix, with parts of them) and the copy fits the kernels' 32-bit offsets
   bool big;           // the large-tile bf16 kernels serve this group (bf16 operand mode, tile-aligned shape): only then
                       // are the bf16 operand copies carved
+  bool k5_direct;     // not big, but bf16 operands and large enough for the update to run on the direct-load core all the same, on
+                      // padded bf16 copies of the factors
   size_t bytes_per_entry;
   Carve carve;     // slot offsets inside one matrix' share of the workspace
   size_t ws_off;   // offset of the group's first matrix in the workspace (set by dion_init_state)
@@ -169,6 +171,23 @@ GramPlan plan_gram_rows(const Group& g, int64_t rows) {
   return gp;
 }
 
+long long round_up(long long x, long long q) { return (x + q - 1) / q * q; }
+// The update of bf16 mode off the large-tile path.  The general core forms it from the fp32 factors, rounding them on the way to
+// the LDS, on tiles of 128 x 64: 2.6 times as many operand bytes as bytes of M, X and G.  The direct-load core's 256 x 128 tile
+// on bf16 copies, padded to whole tiles by a launch more (5-8 us), moves a third as many.  us a step, general core / direct-load:
+//   tiles of 256 x 128 (one matrix)
+//   32-96    1111 x 1733 r = 139  150 / 163;  1500 x 1500 r = 250  169 / 177;  2001 x 1501 r = 300  202 / 207
+//   128      2048 x 2048 r = 200  173 / 177
+//   153-216  2050 x 2050 r = 400  274 / 262;  2049 x 2304 r = 250  196 / 190;  2304 x 2304 r = 100  144 / 143;  9001 x 700 r = 100
+//            188 / 183;  3000 x 2048 r = 64  116 / 117;  16001 x 300 r = 50  192 / 194
+//   256-     3001 x 3001 r = 500  404 / 378;  5003 x 2999 r = 375  429 / 384;  4001 x 4003 r = 20  211 / 202;  8192 x 8192 r = 100
+//            647 / 622;  10001 x 10003 r = 300  2476 / 2267;  Lazy-Dion 5003 x 2999 r = 375  211 / 167
+// A batch of small matrices loses as one alone does (512 x 512 and 512 x 2048, r = 100, eight layers 350 / 403): judged per matrix.
+bool plan_k5_direct(const Group& g) {
+  const long long mp = round_up(g.m, 256), np = round_up(g.n, 128), tiles = (mp / 256) * (np / 128);
+  return tiles >= 144 && (tiles >= 256 || g.r >= 80) && mp < (1ll << 31) && np < (1ll << 31) && std::max(mp, np) * g.rp * 2 < (1ll << 32) &&
+         3ll * g.count <= 65535;
+}
 // lean: nothing that takes workspace only for speed (splits of the products off the large-tile path)
 void plan_gram(Group& g, bool lean) {
   g.k1 = plan_product(g.m, g.r, g.n, g.count, !lean && !g.big);
@@ -229,11 +248,12 @@ Carve carve_entry(const Group& g) {
   take(SLOT_D, g.r);
   // bf16 operand copies (two bf16 values per float slot): only the large-tile bf16 kernels read them
   const size_t b = g.big ? 1 : 0;
+  const size_t kp = g.k5_direct ? (size_t)g.rp : 0, mp = (size_t)round_up(g.m, 256), np = (size_t)round_up(g.n, 128);
   take(SLOT_QT16, b * ((nr + 1) / 2));
-  take(SLOT_P16, b * ((xr + 1) / 2));
+  take(SLOT_P16, b * ((xr + 1) / 2) + mp * kp / 2);
   take(SLOT_PT16, b * ((xr + 1) / 2));
-  take(SLOT_R16, b * ((nr + 1) / 2));
-  take(SLOT_Q16, b * ((nr + 1) / 2));
+  take(SLOT_R16, b * ((nr + 1) / 2) + np * kp / 2);
+  take(SLOT_Q16, b * ((nr + 1) / 2) + np * kp / 2);
   take(SLOT_ZL16, b * ((xr + 1) / 2));
   take(SLOT_ZLT16, b * ((xr + 1) / 2));
   take(SLOT_WH16, b * (((size_t)g.r * g.r + 1) / 2));
@@ -294,6 +314,7 @@ bool build_plan(int count, const int64_t* m, const int64_t* n, const int64_t* r,
     g.first_row = row;
     row += g.count;
     plan_gram(g, lean);
+    g.k5_direct = !g.big && !lean && math == DION_MATH_BF16 && plan_k5_direct(g);
     g.carve = carve_entry(g);
     g.bytes_per_entry = g.carve.total;
   }
@@ -1149,20 +1170,35 @@ int stage_k5(const RowCtx& c, int a16, int b16, int b2_16, int a32, int b32, int
     b2_32 = b32;
   }
   a.status_slot = SLOT_STATUS;
-  if (c.big) {
+  // M, X and G of this call beyond what the 256 MB last-level cache can hold from one step to the next: stream them
+  a.E.stream_hint = (double)c.batch * (double)m * (double)n * 18.0 > 192e6 ? 1 : 0;
+  // Tiles are visited column group by column group, all row tiles of a group before the next group: the n x r column
+  // panels of a group (128 rows x r, two bf16 matrices per tile column) are shared by the tiles that run at the same
+  // time on an XCD and stay in its L2 from one row of tiles to the next.  About 2.5 MB of panels per group, and at
+  // least three tile columns: measured at r = 768 (6 wide), 1024 (5), 2048 and 4096 (3), each against narrower and
+  // wider groups and against the plain row-major order, which costs 10 % at r >= 2048.
+  const int group_n = std::max(3, (int)(2621440LL / (128LL * r * 4)));
+  if (g.k5_direct) {
+    const long long mp = round_up(m, 256), np = round_up(n, 128);
+    const PadJob jobs[3] = {{a32, SLOT_P16, m, mp}, {b32, SLOT_R16, n, np}, {b2_32, SLOT_Q16, n, np}};
+    HIPCHK(launch_pad_bf16(c.tab, NSLOTS, c.batch, jobs, sketch ? 2 : 3, r, g.rp, c.s));
+    a.M = (int)mp; a.N = (int)np; a.K = g.rp;
+    a.E.rows = m; a.E.cols = n;
+    // (rows that share cache lines: what one tile leaves of a line and the next one fills must meet in a cache.  With the hint
+    // 5003 x 2999 r = 375 takes 477 us a step, 384 without; the general core 429)
+    if (n % 32) a.E.stream_hint = 0;
+    a.A = opnd(SLOT_P16, 0, g.rp);
+    a.B = opnd(SLOT_R16, 0, g.rp);
+    a.B2 = opnd(sketch ? SLOT_R16 : SLOT_Q16, 0, g.rp);
+    a.xcd_remap = 1;
+    a.group_n = group_n;
+    HIPCHK(gemm2_k5_ragged(c.gbf16, a, c.batch, c.s));
+  } else if (c.big) {
     a.A = opnd(a16, 0, r);
     a.B = opnd(b16, 0, r);
     a.B2 = opnd(b2_16, 0, r);
     a.xcd_remap = 1;
-    // M, X and G of this call beyond what the 256 MB last-level cache can hold from one step to the next: stream them
-    a.E.stream_hint = (double)c.batch * (double)m * (double)n * 18.0 > 192e6 ? 1 : 0;
-    // Tiles are visited column group by column group, all row tiles of a group before the next group: the n x r column
-    // panels of a group (128 rows x r, two bf16 matrices per tile column) are shared by the tiles that run at the same
-    // time on an XCD and stay in its L2 from one row of tiles to the next.  About 2.5 MB of panels per group, and at
-    // least three tile columns: measured at r = 768 (6 wide), 1024 (5), 2048 and 4096 (3), each against narrower and
-    // wider groups and against the plain row-major order, which costs 10 % at r >= 2048.
-    a.group_n = (int)(2621440LL / (128LL * r * 4));
-    if (a.group_n < 3) a.group_n = 3;
+    a.group_n = group_n;
     // (128x128 tiles, two workgroups per compute unit so that one multiplies while the other streams M, G and X, cost
     // twice the operand traffic of the 256x128 tile and lose or tie at every shape measured: 2 % at 8192 x 8192 r = 512,
     // 10 % at r = 768 and 1024, 20 % at r = 2048, even at 2048 x 2048 r = 512)

@@ -20,12 +20,24 @@ hipError_t gemm2_k5(int cfg, bool gbf16, GemmArgs g, int batch, hipStream_t s) {
   return gbf16 ? launch_gemm2<Mid, SRC2_BF16_KC, true, EPI_UPDATE, true>(g, batch, s)
                : launch_gemm2<Mid, SRC2_BF16_KC, false, EPI_UPDATE, true>(g, batch, s);
 }
+hipError_t gemm2_k5_ragged(bool gbf16, GemmArgs g, int batch, hipStream_t s) {
+  using Direct = TileCfg3<256, 128, 2, 4>;
+  if (g.E.stream_hint)
+    return gbf16 ? launch_gemm3<Direct, true, EPI_UPDATE_RAGGED_STREAM, true>(g, batch, s)
+                 : launch_gemm3<Direct, false, EPI_UPDATE_RAGGED_STREAM, true>(g, batch, s);
+  return gbf16 ? launch_gemm3<Direct, true, EPI_UPDATE_RAGGED, true>(g, batch, s)
+               : launch_gemm3<Direct, false, EPI_UPDATE_RAGGED, true>(g, batch, s);
+}
 hipError_t gemm2_k5_prepare() {
   using Direct = TileCfg3<256, 128, 2, 4>;
   hipError_t e = gemm3_prepare<Direct, true, EPI_UPDATE, true>();
   if (e == hipSuccess) e = gemm3_prepare<Direct, false, EPI_UPDATE, true>();
   if (e == hipSuccess) e = gemm3_prepare<Direct, true, EPI_UPDATE_STREAM, true>();
   if (e == hipSuccess) e = gemm3_prepare<Direct, false, EPI_UPDATE_STREAM, true>();
+  if (e == hipSuccess) e = gemm3_prepare<Direct, true, EPI_UPDATE_RAGGED, true>();
+  if (e == hipSuccess) e = gemm3_prepare<Direct, false, EPI_UPDATE_RAGGED, true>();
+  if (e == hipSuccess) e = gemm3_prepare<Direct, true, EPI_UPDATE_RAGGED_STREAM, true>();
+  if (e == hipSuccess) e = gemm3_prepare<Direct, false, EPI_UPDATE_RAGGED_STREAM, true>();
   return e;
 }
 }  // namespace dion

@@ -41,7 +41,8 @@ enum { SRC_F32_KC = 0, SRC_F32_KS = 1, SRC_SUM_KC = 2, SRC_SUM_KS = 3 };
 // elements (a branch per element: 316 us for the first product, 449 us for the second, 290 us for the update), 639 us so.
 enum { EDGE_EXACT = 0, EDGE_RAGGED = 1, EDGE_CHECKED = 2 };
 // Epilogues.
-enum { EPI_STORE = 0, EPI_UPDATE = 1, EPI_UPDATE_STREAM = 2 };   // the last: direct-load core only, non-temporal M, X, G
+// (the last three: direct-load core only.  STREAM: non-temporal M, X, G.  RAGGED: M, X, G of any size and row alignment)
+enum { EPI_STORE = 0, EPI_UPDATE = 1, EPI_UPDATE_STREAM = 2, EPI_UPDATE_RAGGED = 3, EPI_UPDATE_RAGGED_STREAM = 4 };
 
 struct Operand {
   int slot0;            // pointer-table slot of the fp32 matrix
@@ -64,6 +65,7 @@ struct EpilogueDesc {
   int split_hi1, split_lo1;   // EPI_STORE of the direct-load core, whole products only: slot + 1 (0: none) of two bf16
                         // matrices of the result's shape and leading dimension that receive the result split as
                         // x = hi + lo, hi = bf16(x), lo = bf16(x - hi): the operands of a split-bf16 product that follows
+  int rows, cols;       // EPI_UPDATE_RAGGED*: size of M, X and G; the product's is rounded up to whole tiles, its operands padded
   int stream_hint;      // host side: take the EPI_UPDATE_STREAM kernel (M, X and G loaded and stored with the
                         // non-temporal hint; for working sets far beyond the last-level cache)
 };

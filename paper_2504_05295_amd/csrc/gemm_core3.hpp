@@ -19,6 +19,7 @@
 // to the compiler, every LDS read would wait for all loads in flight, since it cannot tell their LDS
 // destinations apart.
 #pragma once
+#include <type_traits>
 #include <algorithm>
 
 #include "gemm_core.hpp"
@@ -444,11 +445,16 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::MINW) gemm3_kernel(const GemmArg
       f32x4_t mv[4], xv[4];
       u32x4_t gw[4];   // G as loaded: four fp32 values, or four bf16 values in the first two words
     };
-    auto block_index = [&](int t, int p) __attribute__((always_inline)) {
-      const int i = t / NI, j = t % NI;
-      const int row = row0 + wm * Cfg::WTM + i * 32 + prow + 8 * p;
-      const int col = col0 + wn * Cfg::WTN + j * 32 + pcol;
-      return (long long)row * g.E.ld + col;
+    constexpr bool RAGGED = EPI == EPI_UPDATE_RAGGED || EPI == EPI_UPDATE_RAGGED_STREAM;
+    using F4 = typename std::conditional<RAGGED, f32x4_any_t, f32x4_t>::type;
+    using U4 = typename std::conditional<RAGGED, u32x4_any_t, u32x4_t>::type;
+    using U2 = typename std::conditional<RAGGED, u32x2_any_t, u32x2_t>::type;
+    auto block_row = [&](int t, int p) __attribute__((always_inline)) { return row0 + wm * Cfg::WTM + (t / NI) * 32 + prow + 8 * p; };
+    auto block_col = [&](int t) __attribute__((always_inline)) { return col0 + wn * Cfg::WTN + (t % NI) * 32 + pcol; };
+    auto block_index = [&](int t, int p) __attribute__((always_inline)) { return (long long)block_row(t, p) * g.E.ld + block_col(t); };
+    // RAGGED: how many of a lane's four columns exist (a row beyond the last has none)
+    auto inside = [&](int t, int p) __attribute__((always_inline)) {
+      return !RAGGED ? 4 : block_row(t, p) >= g.E.rows ? 0 : max(0, min(4, g.E.cols - block_col(t)));
     };
     auto g_value = [&](const u32x4_t& w) __attribute__((always_inline)) {
       if constexpr (GBF16) return f32x4_t{bf16_lo(w[0]), bf16_hi(w[0]), bf16_lo(w[1]), bf16_hi(w[1])};
@@ -457,22 +463,51 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::MINW) gemm3_kernel(const GemmArg
     // (the hint is a compile-time choice: a select between a hinted and a plain load would issue both, and two copies
     // of the pass inside one kernel cost registers)
     {
-      constexpr bool NTH = EPI == EPI_UPDATE_STREAM;
+      constexpr bool NTH = EPI == EPI_UPDATE_STREAM || EPI == EPI_UPDATE_RAGGED_STREAM;
       auto load_block = [&](int t, BlockIn& in) __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
           const long long idx = block_index(t, p);
-          in.mv[p] = NTH ? gload_nt<f32x4_t>(Mp + idx) : gload<f32x4_t>(Mp + idx);
-          if constexpr (DUAL) {
-            if (g.E.x_overwrite) in.xv[p] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            else in.xv[p] = NTH ? gload_nt<f32x4_t>(Xp + idx) : gload<f32x4_t>(Xp + idx);
-          }
-          if constexpr (GBF16) {
-            const u32x2_t w = NTH ? gload_nt<u32x2_t>((const uint16_t*)Gp + idx) : gload<u32x2_t>((const uint16_t*)Gp + idx);
-            in.gw[p] = u32x4_t{w[0], w[1], 0u, 0u};
+          const int nc = inside(t, p);
+          if (!RAGGED || nc == 4) {
+            in.mv[p] = NTH ? gload_nt<F4>(Mp + idx) : gload<F4>(Mp + idx);
+            if constexpr (DUAL) {
+              if (g.E.x_overwrite) in.xv[p] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+              else in.xv[p] = NTH ? gload_nt<F4>(Xp + idx) : gload<F4>(Xp + idx);
+            }
+            if constexpr (GBF16) {
+              const u32x2_t w = NTH ? gload_nt<U2>((const uint16_t*)Gp + idx) : gload<U2>((const uint16_t*)Gp + idx);
+              in.gw[p] = u32x4_t{w[0], w[1], 0u, 0u};
+            } else {
+              in.gw[p] = NTH ? gload_nt<U4>((const float*)Gp + idx) : gload<U4>((const float*)Gp + idx);
+            }
           } else {
-            in.gw[p] = NTH ? gload_nt<u32x4_t>((const float*)Gp + idx) : gload<u32x4_t>((const float*)Gp + idx);
+            in.mv[p] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if constexpr (DUAL) in.xv[p] = in.mv[p];
+            in.gw[p] = u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+              if (e >= nc) continue;
+              in.mv[p][e] = gload<float>(Mp + idx + e);
+              if constexpr (DUAL) {
+                if (!g.E.x_overwrite) in.xv[p][e] = gload<float>(Xp + idx + e);
+              }
+              if constexpr (GBF16) in.gw[p][e >> 1] |= (uint32_t)gload<uint16_t>((const uint16_t*)Gp + idx + e) << (16 * (e & 1));
+              else in.gw[p][e] = gload<uint32_t>((const float*)Gp + idx + e);
+            }
           }
+        }
+      };
+      auto store = [&](float* out, int t, int p, const f32x4_t& v) __attribute__((always_inline)) {
+        const long long idx = block_index(t, p);
+        const int nc = inside(t, p);
+        if (!RAGGED || nc == 4) {
+          if constexpr (NTH) gstore_nt<F4>(out + idx, v);
+          else gstore<F4>(out + idx, v);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (e < nc) gstore<float>(out + idx + e, v[e]);
         }
       };
       constexpr int NBLK = MI * NI;
@@ -487,8 +522,7 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::MINW) gemm3_kernel(const GemmArg
         for (int p = 0; p < 4; ++p) {
           const f32x4_t a4 = *(const f32x4_t*)(patch + (prow + 8 * p) * SP + pcol);
           const f32x4_t mn = (c.mv[p] + g_value(c.gw[p])) - g.E.c_m * a4;
-          if constexpr (NTH) gstore_nt<f32x4_t>(Mp + block_index(t, p), mn);
-          else gstore<f32x4_t>(Mp + block_index(t, p), mn);
+          store(Mp, t, p, mn);
         }
         if constexpr (DUAL) {
           to_patch(acc2[t / NI][t % NI]);
@@ -496,8 +530,7 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::MINW) gemm3_kernel(const GemmArg
           for (int p = 0; p < 4; ++p) {
             const f32x4_t a4 = *(const f32x4_t*)(patch + (prow + 8 * p) * SP + pcol);
             const f32x4_t xn = c.xv[p] - g.E.c_x * a4;
-            if constexpr (NTH) gstore_nt<f32x4_t>(Xp + block_index(t, p), xn);
-            else gstore<f32x4_t>(Xp + block_index(t, p), xn);
+            store(Xp, t, p, xn);
           }
         }
       }

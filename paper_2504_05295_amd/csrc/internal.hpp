@@ -91,6 +91,9 @@ enum { G2_256x256 = 0, G2_128x128 = 1, G2_256x128 = 2 };   // (the last one: gem
 hipError_t gemm2_k1(int cfg, bool gbf16, GemmArgs g, int batch, hipStream_t s);
 hipError_t gemm2_k2(int cfg, bool gbf16, GemmArgs g, int batch, hipStream_t s, bool from_bf16 = false);   // from_bf16: A = bf16 [K][M]
 hipError_t gemm2_k5(int cfg, bool gbf16, GemmArgs g, int batch, hipStream_t s);
+// the same for M, X and G of any size (E.rows x E.cols): g.M x g.N is that size rounded up to whole 256 x 128 tiles, g.K to a multiple
+// of 64, and the bf16 operands are padded to it (launch_pad_bf16)
+hipError_t gemm2_k5_ragged(bool gbf16, GemmArgs g, int batch, hipStream_t s);
 int gemm2_k1_splitk(int cfg, const GemmArgs& g);   // number of split-K partials the launch will write
 int gemm2_k2_splitk(int cfg, const GemmArgs& g);
 // measured ceilings: bf16 MFMA issue loop (TFLOP/s) and an 18-byte-per-element streaming pass (GB/s); synchronises
@@ -177,6 +180,9 @@ hipError_t launch_split_bf16(void* const* table, int nslots, int batch, int slot
                              int skip_slot = -1);   // skip_slot >= 0: nothing happens for matrices whose int32 there is non-zero
 hipError_t launch_convert_bf16(void* const* table, int nslots, int batch, int slot_in, int slot_out16, int slot_outT16,
                                long long rows, long long cols, hipStream_t s, int skip_slot = -1);
+// Up to three matrices at once: fp32 [rows][cols] -> bf16 [rows_out][cols_out], zeros beyond (cols_out a multiple of 8)
+struct PadJob { int slot_in, slot_out; long long rows, rows_out; };
+hipError_t launch_pad_bf16(void* const* table, int nslots, int batch, const PadJob* jobs, int njobs, int cols, int cols_out, hipStream_t s);
 hipError_t launch_gaussian_fill(void* const* table, int nslots, int batch, int slot, long long count, uint64_t seed,
                                 int first_stream, hipStream_t s);
 // Buffers of the first matrix of a batch; matrix b has them `stride` 4-byte words further (status: b ints further).

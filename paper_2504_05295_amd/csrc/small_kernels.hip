@@ -788,6 +788,49 @@ hipError_t launch_first_order_inverse(void* const* table, int nslots, int batch,
   return hipGetLastError();
 }
 
+// Padded bf16 operand copies for the update of ragged shapes on the direct-load core: a thread forms eight consecutive
+// columns of a row.  Bound by the launch and one pass over the factors (5003 x 375 and two of 2999 x 375: 17 MB in, 9 MB out).
+struct PadJobs { PadJob j[3]; };
+__global__ void __launch_bounds__(256) pad_bf16_kernel(void* const* table, int nslots, const PadJobs jobs, int njobs, int cols, int cols_out) {
+  const int b = blockIdx.y / njobs;
+  const PadJob job = jobs.j[blockIdx.y % njobs];
+  void* const* tab = table + (size_t)b * nslots;
+  const float* in = (const float*)tab[job.slot_in];
+  uint16_t* out = (uint16_t*)tab[job.slot_out];
+  const int per_row = cols_out / 8;
+  const long long total = job.rows_out * per_row;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+    const long long row = i / per_row;
+    const int c = (int)(i - row * per_row) * 8;
+    f32x4_t v[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    if (row < job.rows) {
+      const float* p = in + row * cols + c;
+      if (c + 8 <= cols) {
+        v[0] = gload<f32x4_any_t>(p);
+        v[1] = gload<f32x4_any_t>(p + 4);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 7; ++e)
+          if (c + e < cols) v[e >> 2][e & 3] = gload<float>(p + e);
+      }
+    }
+    gstore<u32x4_t>(out + row * cols_out + c, u32x4_t{pack_bf16x2(v[0][0], v[0][1]), pack_bf16x2(v[0][2], v[0][3]),
+                                                      pack_bf16x2(v[1][0], v[1][1]), pack_bf16x2(v[1][2], v[1][3])});
+  }
+}
+hipError_t launch_pad_bf16(void* const* table, int nslots, int batch, const PadJob* jobs, int njobs, int cols, int cols_out, hipStream_t s) {
+  if (njobs < 1 || njobs > 3 || cols_out % 8 || cols > cols_out || (long long)njobs * batch > GRID_Y_MAX) return hipErrorInvalidValue;
+  PadJobs p = {};
+  long long most = 0;
+  for (int i = 0; i < njobs; ++i) {
+    p.j[i] = jobs[i];
+    most = std::max(most, jobs[i].rows_out * (cols_out / 8));
+  }
+  const unsigned blocks = (unsigned)std::min<long long>((most + 255) / 256, 4096);
+  hipLaunchKernelGGL(pad_bf16_kernel, dim3(blocks, njobs * batch), dim3(256), 0, s, table, nslots, p, njobs, cols, cols_out);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- Gaussian fill (Philox-4x32-10 + Box-Muller)
 __device__ __forceinline__ void philox_round(uint32_t (&c)[4], uint32_t k0, uint32_t k1) {
   const uint64_t p0 = (uint64_t)0xD2511F53u * c[0];
