@@ -201,7 +201,7 @@ __device__ __forceinline__ void chain_wave(lds_float* S, lds_counter* sync, int 
     announce(sync + W_DONE, s + 1);
     if constexpr (s < 3) {
       const f32x4_t l = mm_short(ZERO, sub, w);
-      diag = mm_short(next, -l, l);
+      diag = next - mm_short(ZERO, l, l);   // (the sum by itself: with `next` in the accumulator its parts are rounded at next's size)
     } else {
       wait_for(sync + SUM_DONE, 1);
       last_row_tile(S, 2, lane, w);
@@ -241,9 +241,8 @@ __device__ __forceinline__ void update_wave(lds_float* S, lds_counter* sync, int
     static_for<q + 1, 4>([&](auto ic) __attribute__((always_inline)) { L[decltype(ic)::value][q] = mm(ZERO, T[decltype(ic)::value][q], W); });
     // (the chain has read tiles (q + 1, q) and (q + 1, q + 1) before it announced W_qq)
     if constexpr (q < 2) {
-      const f32x4_t neg = -L[q + 2][q];
-      T[q + 2][q + 1] = mm(T[q + 2][q + 1], neg, L[q + 1][q]);
-      T[q + 2][q + 2] = mm(T[q + 2][q + 2], neg, L[q + 2][q]);
+      T[q + 2][q + 1] -= mm(ZERO, L[q + 2][q], L[q + 1][q]);
+      T[q + 2][q + 2] -= mm(ZERO, L[q + 2][q], L[q + 2][q]);
       *tile_at(S, q + 2, q + 1, lane) = T[q + 2][q + 1];
       *tile_at(S, q + 2, q + 2, lane) = T[q + 2][q + 2];
       announce(sync + T_DONE, q + 2);
@@ -252,11 +251,9 @@ __device__ __forceinline__ void update_wave(lds_float* S, lds_counter* sync, int
       static_for<q + 1, 4>([&](auto ic) __attribute__((always_inline)) { *tile_at(S, decltype(ic)::value, q, lane) = L[decltype(ic)::value][q]; });
       announce(sync + L_DONE, q + 1);
       // the rest of the updates; T_{q+1,q+1} once more, for its L
-      T[q + 1][q + 1] = mm(T[q + 1][q + 1], -L[q + 1][q], L[q + 1][q]);
-      if constexpr (q == 0) {
-        const f32x4_t neg = -L[3][0];
-        static_for<1, 4>([&](auto jc) __attribute__((always_inline)) { T[3][decltype(jc)::value] = mm(T[3][decltype(jc)::value], neg, L[decltype(jc)::value][0]); });
-      }
+      T[q + 1][q + 1] -= mm(ZERO, L[q + 1][q], L[q + 1][q]);
+      if constexpr (q == 0)
+        static_for<1, 4>([&](auto jc) __attribute__((always_inline)) { T[3][decltype(jc)::value] -= mm(ZERO, L[3][0], L[decltype(jc)::value][0]); });
     } else {
       wait_for(sync + SUM_DONE, 1);
       last_row_tile(S, 1, lane, W);

@@ -157,45 +157,58 @@ __global__ void __launch_bounds__(256, 2) chol_panel_kernel(CholPanelPtrs p, int
 // panel, two products per merge of the inverse, one to add up the partial Gram matrices and one to pad, and an adaptive
 // pass as many again, most of them only to find out that there was nothing to do.  The lower triangle of the matrix
 // lives in LDS (six tiles, 102 KB); tile (k, k) turns into W11(k), tile (i, k) into L[i][k] and, once row i of
-// the inverse is through, into W(i, k).  What bounds it is the chain of the diagonal blocks (9.6 us each) and, with it,
-// about three tile products per panel (1 us each).  Per step k, with a barrier after each line:
+// the inverse is through, into W(i, k).  What bounds it is the chain of the diagonal blocks (3.7 us each) and the tile products,
+// about 600 of 16 x 16 x 16 at three panels, 8 us of the compute unit's fp32 matrix units.  Per step k, with a barrier after each line:
 //   D(k);   L[i][k] = C[i][k] W11^T (i > k)  and  Y(e) = sum_{e <= p < k} L[k][p] W(p, e) (e < k), in registers;   both to LDS
 //   C[i][j] -= L[i][k] L[j][k]^T (i >= j > k)  and  W(k, e) = -W11 Y(e);   W(k, e) to LDS
+// by eight waves, on 16 x 16 tiles in the register layout of chol_block.hpp, zero ones of W11 and those above the diagonal left
+// out: the first line by strips of sixteen rows (wave % 4) and tiles (wave / 4), the second tile by tile.  A step against four
+// waves with a 32 x 32 quadrant of every 64 x 64 product each: 1111 x 1733 r = 139 in fp32 170 -> 158 us, two layers of d = 768,
+// r = 192 360 -> 346, 256 x 256 r = 64 in fp32 70.1 -> 68.7.
 // FAST DECISION (adaptive, i.e. tau2 > 0): as launch_first_order_inverse describes it, in here.
-// Measured: the launch takes 13 / 61 us at one / three panels, 4.4 / 9 us where the pass is cut short.  A step with the
-// launches it replaces / with it: 256 x 256 r = 64 in fp32 88.2 / 78.0 us, 1111 x 1733 r = 139 in fp32 214 / 193 us, two layers of
-// d = 768, r = 192 in one call 687 / 625 us.
 template <int NB>
-__global__ void __launch_bounds__(256, 1) chol_small_kernel(CholSmallArgs p) {
+__global__ void __launch_bounds__(512, 2) chol_small_kernel(CholSmallArgs p) {
   const long long mat = (long long)blockIdx.x * p.stride;
   if (p.skip && p.skip[mat] != 0) return;   // uniform
+  using chol_block::mm;
+  using chol_block::ZERO;
   constexpr int TILES = NB * (NB + 1) / 2;
   __shared__ __attribute__((aligned(16))) float T[TILES][CB * CBP];
-  __shared__ float red[256];
+  __shared__ float red[512];
   __shared__ volatile int sync[chol_block::COUNTERS];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int wm = wave & 1, wn = wave >> 1, lr = lane & 31, lk = lane >> 5;
-  const int frow = wm * 32 + 4 * lk, fcol = wn * 32 + lr;
+  const int c16 = lane & 15, g4 = 4 * (lane >> 4);
   const int ld = p.rp, r = p.r;
   float* C = p.C + mat;
   float* L = p.L + mat;
   float* W = p.W + mat;
   auto tile = [&](int i, int j) __attribute__((always_inline)) -> float* { return T[i * (i + 1) / 2 + j]; };
+  auto sub = [&](float* S, int i, int j) __attribute__((always_inline)) -> lds_f32x4* { return chol_block::tile_at((lds_float*)S, i, j, lane); };
+  // the transpose of 16 x 16 tile (i, j) of S: with it as the right operand mm adds Y S(i, j)
+  auto sub_t = [&](const float* S, int i, int j) __attribute__((always_inline)) {
+    f32x4_t x;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = S[(16 * i + g4 + v) * CBP + 16 * j + c16];
+    return x;
+  };
+  auto at = [&](float* M, int i, int j, int si, int sj) __attribute__((always_inline)) {   // this lane's four entries of tile (si, sj) of tile (i, j)
+    return (f32x4_t*)(M + (long long)(i * CB + 16 * si + c16) * ld + j * CB + 16 * sj + g4);
+  };
   // The lower tiles in: the loads of all tiles and of UN splits are in flight together (tile by tile the cut-short pass took
   // 11 us at three panels, five of them round trips to memory); partial results are added up in the order of the splits.
   // Rows and columns from r up become the identity's, entries above the diagonal zero.
-  constexpr int UN = NB == 1 ? 4 : 1;
+  constexpr int UN = NB == 1 ? 4 : 2;
   const int trow = t >> 4, tcol = (t & 15) * 4;
-  f32x4_t acc[TILES][4];
+  f32x4_t acc[TILES][2];
 #pragma unroll
   for (int x = 0; x < TILES; ++x)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[x][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < 2; ++q) acc[x][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   {
     const float* src = (p.nsplit > 1 ? p.Cpart + mat : C) + (long long)trow * ld + tcol;
 #pragma unroll 1
     for (int sp = 0; sp < p.nsplit; sp += UN) {
-      f32x4_t v[UN][TILES][4];
+      f32x4_t v[UN][TILES][2];
 #pragma unroll
       for (int u = 0; u < UN; ++u)
 #pragma unroll
@@ -203,18 +216,18 @@ __global__ void __launch_bounds__(256, 1) chol_small_kernel(CholSmallArgs p) {
 #pragma unroll
           for (int j = 0; j <= i; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < 2; ++q) {
               f32x4_t& w = v[u][i * (i + 1) / 2 + j][q];
               w = f32x4_t{0.f, 0.f, 0.f, 0.f};
               if (sp + u < p.nsplit)
-                w = *(const f32x4_t*)(src + (long long)(sp + u) * p.split_stride + (long long)(i * CB + 16 * q) * ld + j * CB);
+                w = *(const f32x4_t*)(src + (long long)(sp + u) * p.split_stride + (long long)(i * CB + 32 * q) * ld + j * CB);
             }
 #pragma unroll
       for (int u = 0; u < UN; ++u)
 #pragma unroll
         for (int x = 0; x < TILES; ++x)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) acc[x][q] += v[u][x][q];
+          for (int q = 0; q < 2; ++q) acc[x][q] += v[u][x][q];
     }
   }
   float dist = 0.f;
@@ -223,9 +236,9 @@ __global__ void __launch_bounds__(256, 1) chol_small_kernel(CholSmallArgs p) {
 #pragma unroll
     for (int j = 0; j <= i; ++j)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < 2; ++q) {
         f32x4_t& c = acc[i * (i + 1) / 2 + j][q];
-        const int row = i * CB + trow + 16 * q;
+        const int row = i * CB + trow + 32 * q;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int col = j * CB + tcol + e;
@@ -236,13 +249,13 @@ __global__ void __launch_bounds__(256, 1) chol_small_kernel(CholSmallArgs p) {
             dist += (row == col ? 1.f : 2.f) * d * d;
           }
         }
-        *(f32x4_t*)(tile(i, j) + (trow + 16 * q) * CBP + tcol) = c;
+        *(f32x4_t*)(tile(i, j) + (trow + 32 * q) * CBP + tcol) = c;
         if (p.nsplit > 1) *(f32x4_t*)(C + (long long)row * ld + j * CB + tcol) = c;
       }
   if (p.tau2 > 0.f) {
     red[t] = dist;
     __syncthreads();
-    for (int sft = 128; sft > 0; sft >>= 1) {
+    for (int sft = 256; sft > 0; sft >>= 1) {
       if (t < sft) red[t] += red[t + sft];
       __syncthreads();
     }
@@ -250,33 +263,25 @@ __global__ void __launch_bounds__(256, 1) chol_small_kernel(CholSmallArgs p) {
     if (t == 0) p.fast[mat] = fast ? 1 : 0;
     if (fast) {
       if (!p.decision_only)
+#pragma unroll
         for (int i = 0; i < NB; ++i)
+#pragma unroll
           for (int j = 0; j <= i; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int rr = (t >> 4) + 16 * q, cc = (t & 15) * 4;
-              f32x4_t v = *(const f32x4_t*)(tile(i, j) + rr * CBP + cc);
+            for (int q = 0; q < 2; ++q) {
+              const int rr = trow + 32 * q;
+              f32x4_t v = acc[i * (i + 1) / 2 + j][q];
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                if (i != j || cc + e != rr) v[e] = -v[e];
+                if (i != j || tcol + e != rr) v[e] = -v[e];
                 else v[e] = 1.f - 0.5f * (v[e] - 1.f);
               }
-              *(f32x4_t*)(W + (long long)(i * CB + rr) * ld + j * CB + cc) = v;
+              *(f32x4_t*)(W + (long long)(i * CB + rr) * ld + j * CB + tcol) = v;
             }
       return;   // uniform
     }
   }
-  // acc += A B for LDS tiles, B with k as its slow index
-  auto mma_nn = [&](const float* A, const float* B, f32x16_t acc) __attribute__((always_inline)) {
-#pragma unroll
-    for (int kk = 0; kk < CB; kk += 8) {
-      const f32x4_t a = *(const f32x4_t*)(A + (wm * 32 + lr) * CBP + kk + lk * 4);
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], B[(kk + lk * 4 + s) * CBP + wn * 32 + lr], acc, 0, 0, 0);
-    }
-    return acc;
-  };
+  const int q = wave & 3, half = wave >> 2;
 #pragma unroll 1   // (three copies of the diagonal block's code are more than the instruction cache holds)
   for (int k = 0; k < NB; ++k) {
     float* S0 = tile(k, k);
@@ -285,66 +290,108 @@ __global__ void __launch_bounds__(256, 1) chol_small_kernel(CholSmallArgs p) {
     chol_block::factor_invert<false>(S0, (chol_block::lds_counter*)sync, wave, lane, p.piv_lo, p.piv_hi, L + (long long)k * CB * (ld + 1), ld,
                                      p.status + blockIdx.x, 0.f, nullptr);
     __syncthreads();
+    // rows 16 q of one of the NB - 1 tiles of this line: the tiles L[i][k], i > k, then the sums Y(e), e < k
+    f32x4_t out[4] = {ZERO, ZERO, ZERO, ZERO};
+    const int i1 = k + 1 + half, e1 = i1 - NB;   // i1 < NB: L[i1][k]; else, e1 < k: Y(e1)
+    if (i1 < NB) {
+      f32x4_t y[4], w[10];   // (operands are read ahead of the products: see mma_64)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int rr = (t >> 4) + 16 * q, cc = (t & 15) * 4;
-      *(f32x4_t*)(W + (long long)(k * CB + rr) * ld + k * CB + cc) = *(const f32x4_t*)(S0 + rr * CBP + cc);
-    }
-    f32x16_t li[NB], y[NB];   // indexed by row i > k and by column e < k
+      for (int e = 0; e < 4; ++e) y[e] = *sub(tile(i1, k), q, e);
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) y[i][v] = 0.f;
-      if (i > k) li[i] = mma_64(tile(i, k), S0, wm, wn, lr, lk);
-      if (i < k)
+        for (int e = 0; e <= j; ++e) w[j * (j + 1) / 2 + e] = *sub(S0, j, e);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e <= j; ++e) out[j] = mm(out[j], y[e], w[j * (j + 1) / 2 + e]);
+    } else if (e1 < k) {
 #pragma unroll 1
-        for (int q = i; q < k; ++q) y[i] = mma_nn(tile(k, q), tile(q, i), y[i]);
+      for (int m = e1; m < k; ++m) {
+        f32x4_t y[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = *sub(tile(k, m), q, e);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          f32x4_t x[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = sub_t(tile(m, e1), e, j);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (m > e1 || e >= j) out[j] = mm(out[j], y[e], x[e]);   // (W11(e1) is lower triangular)
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e)   // W11 out
+      *(f32x4_t*)(W + (long long)(k * CB + trow + 32 * e) * ld + k * CB + tcol) = *(const f32x4_t*)(S0 + (trow + 32 * e) * CBP + tcol);
+    __syncthreads();
+    if (i1 < NB) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        *sub(tile(i1, k), q, j) = out[j];
+        *at(L, i1, k, q, j) = out[j];
+      }
+    } else if (e1 < k) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) *sub(tile(k, e1), q, j) = out[j];
     }
     __syncthreads();
+    // the updates, their 16 x 16 tiles dealt out to the waves
+    int n = wave;
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
+    for (int i = 1; i < NB; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = frow + 8 * (v / 4) + (v % 4);
-        if (i > k) {
-          tile(i, k)[row * CBP + fcol] = li[i][v];
-          L[(long long)(i * CB + row) * ld + k * CB + fcol] = li[i][v];
-        }
-        if (i < k) tile(k, i)[row * CBP + fcol] = y[i][v];
-      }
-    __syncthreads();
+      for (int j = 1; j <= i; ++j) {
+        if (j <= k) continue;   // (uniform)
+        const int count = i == j ? 10 : 16;
+        for (; n < count; n += 8) {
+          const int si = i != j ? n >> 2 : n >= 6 ? 3 : n >= 3 ? 2 : n >= 1 ? 1 : 0, sj = i != j ? n & 3 : n - si * (si + 1) / 2;
+          const f32x4_t old = *sub(tile(i, j), si, sj);
+          f32x4_t c = ZERO, y[4], x[4];   // (summed up by itself: with `old` in the accumulator every partial sum is rounded at its size)
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      if (i < k) {
-        f32x16_t z;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) z[v] = 0.f;
-        y[i] = mma_nn(S0, tile(k, i), z);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          y[i][v] = -y[i][v];
-          W[(long long)(k * CB + frow + 8 * (v / 4) + (v % 4)) * ld + i * CB + fcol] = y[i][v];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-        if (j > k && j <= i) {
-          const f32x16_t up = mma_64(tile(i, k), tile(j, k), wm, wn, lr, lk);
-          float* c = tile(i, j);
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int row = frow + 8 * (v / 4) + (v % 4);
-            c[row * CBP + fcol] = (i != j || fcol <= row) ? c[row * CBP + fcol] - up[v] : 0.f;
+          for (int e = 0; e < 4; ++e) {
+            y[e] = *sub(tile(i, k), si, e);
+            x[e] = *sub(tile(j, k), sj, e);
           }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) c = mm(c, y[e], x[e]);
+          *sub(tile(i, j), si, sj) = old - c;
         }
+        n -= count;
+      }
+    // W(k, e) = -W11 Y(e): tiles (half, q) and (half + 2, q)
+    f32x4_t z[NB > 1 ? NB - 1 : 1][2];
+#pragma unroll
+    for (int e1 = 0; e1 + 1 < NB; ++e1) {
+      if (e1 >= k) continue;   // (uniform)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int si = half + 2 * u;
+        f32x4_t y[4], x[4], c = ZERO;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          y[e] = *sub(S0, si, e);
+          x[e] = sub_t(tile(k, e1), e, q);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e <= si) c = mm(c, y[e], x[e]);
+        z[e1][u] = -c;
+        *at(W, k, e1, si, q) = z[e1][u];
+      }
     }
     if (k > 0 && k + 1 < NB) {
       __syncthreads();   // row k of Y is read
 #pragma unroll
-      for (int i = 0; i < NB; ++i)
-        if (i < k)
+      for (int e1 = 0; e1 + 1 < NB; ++e1)
+        if (e1 < k)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) tile(k, i)[(frow + 8 * (v / 4) + (v % 4)) * CBP + fcol] = y[i][v];
+          for (int u = 0; u < 2; ++u) *sub(tile(k, e1), half + 2 * u, q) = z[e1][u];
     }
   }
 }
@@ -352,9 +399,9 @@ __global__ void __launch_bounds__(256, 1) chol_small_kernel(CholSmallArgs p) {
 hipError_t launch_chol_small(CholSmallArgs p, int batch, hipStream_t s) {
   if (p.nsplit < 1 || p.rp % CB || p.r > p.rp || p.split_stride % 4) return hipErrorInvalidValue;
   switch (p.rp / CB) {
-    case 1: hipLaunchKernelGGL(chol_small_kernel<1>, dim3(batch), dim3(256), 0, s, p); break;
-    case 2: hipLaunchKernelGGL(chol_small_kernel<2>, dim3(batch), dim3(256), 0, s, p); break;
-    case 3: hipLaunchKernelGGL(chol_small_kernel<3>, dim3(batch), dim3(256), 0, s, p); break;
+    case 1: hipLaunchKernelGGL(chol_small_kernel<1>, dim3(batch), dim3(512), 0, s, p); break;
+    case 2: hipLaunchKernelGGL(chol_small_kernel<2>, dim3(batch), dim3(512), 0, s, p); break;
+    case 3: hipLaunchKernelGGL(chol_small_kernel<3>, dim3(batch), dim3(512), 0, s, p); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -940,7 +987,8 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
       // the next diagonal block (its lower triangle): ten tiles, numbered along the rows, wave w takes w and, of them, 8 and 9
       for (int n = wave; n < 10; n += 8) {
         const int i = n >= 6 ? 3 : n >= 3 ? 2 : n >= 1 ? 1 : 0, j = n - i * (i + 1) / 2;
-        f32x4_t c = -*sub(SD, i, j), yl[4], xl[4];
+        const f32x4_t old = *sub(SD, i, j);
+        f32x4_t c = ZERO, yl[4], xl[4];   // (summed up by itself: with `old` in the accumulator every partial sum is rounded at its size)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           yl[e] = *sub(SL, i, e);
@@ -949,7 +997,7 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < 4; ++e) c = mm(c, yl[e], xl[e]);
-        *sub(S0, i, j) = -c;
+        *sub(S0, i, j) = old - c;
       }
       if (wave >= 4 && last_of(1, 4)) flag_store(x.lflag + k + 1, ep32 | (u64)(k + 1));   // (they have one tile each: no time lost)
 #ifdef DION_CHOL_TIMING
