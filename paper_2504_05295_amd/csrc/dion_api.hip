@@ -811,10 +811,17 @@ struct RowCtx {
   GemmArgs base;
   hipEvent_t* ev;   // start / end event per stage, or nullptr
   hipStream_t s;
+  mutable FirstTouch first;   // for the first launch of the call, which takes it (row == nullptr: nothing to take)
+  FirstTouch take_first() const {
+    const FirstTouch f = first;
+    first = FirstTouch{};
+    return f;
+  }
 };
 
-RowCtx make_ctx(dion_state* st, int gi, int row0, int batch, hipStream_t s) {
+RowCtx make_ctx(dion_state* st, int gi, int row0, int batch, hipStream_t s, const FirstTouch& first) {
   RowCtx c;
+  c.first = first;
   c.st = st; c.g = &st->groups[gi]; c.gi = gi; c.row0 = row0; c.batch = batch; c.s = s;
   c.tab = st->table + (size_t)(c.g->first_row + row0) * NSLOTS;
   c.bf16 = st->math == DION_MATH_BF16;
@@ -849,7 +856,7 @@ bool direct12(const RowCtx& c) {
 // The bf16 copy of M + G for the K1 / K2 of this call (a no-op off the direct-load path).
 int stage_b16(const RowCtx& c) {
   if (!direct12(c)) return DION_OK;
-  HIPCHK(launch_sum_bf16(c.tab, NSLOTS, c.batch, SLOT_M, SLOT_G, c.gbf16, SLOT_B16, c.g->m, c.g->n, c.s));
+  HIPCHK(launch_sum_bf16(c.tab, NSLOTS, c.batch, SLOT_M, SLOT_G, c.gbf16, SLOT_B16, c.g->m, c.g->n, c.s, c.take_first()));
   return DION_OK;
 }
 
@@ -916,6 +923,7 @@ hipError_t run_product(const RowCtx& c, ProductFn fn, const ProductPlan& p, Gemm
   }
   // (the whole group: as planned, with the split that was allowed for, of which rounding may have left fewer parts)
   const int variant = c.batch == c.g->count ? p.variant : product_variant(a.M, a.N, a.K, c.batch, p.splitk);
+  a.first = c.take_first();
   const hipError_t e = fn(variant, c.bf16, c.gbf16, a, c.batch, c.s);
   if (e != hipSuccess || p.splitk == 1) return e;
   return finish_split(c, slot_out, a.E.split_stride, p.splitk, pending);
@@ -986,7 +994,7 @@ int stage_k1(const RowCtx& c, bool keep_b16, int slot_q = SLOT_Q, bool split_out
       }
       return DION_OK;
     }
-    HIPCHK(launch_convert_bf16(c.tab, NSLOTS, c.batch, slot_q, -1, SLOT_QT16, n, r, c.s));
+    HIPCHK(launch_convert_bf16(c.tab, NSLOTS, c.batch, slot_q, -1, SLOT_QT16, n, r, c.s, -1, c.take_first()));
     a.B = opnd(SLOT_QT16, 0, n);
     if (keep_b16) a.side_slot = SLOT_B16;
     const int c1 = tile_cfg2(c, m, r);
@@ -1225,8 +1233,9 @@ int stage_k5(const RowCtx& c, int a16, int b16, int b2_16, int a32, int b32, int
 //                    columns, since this stage's buffer is a sum of a few low-rank sketches at first (stage 2)
 // The status words are cleared by the kernel that refreshes the pointer table before the step.
 enum { STEP_PLAIN = 0, STEP_SKETCH = 1, STEP_KEEP_STATUS = 2 };
-int step_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, hipStream_t s, int mode = STEP_PLAIN) {
-  const RowCtx c = make_ctx(st, gi, row0, batch, s);
+int step_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, hipStream_t s, int mode = STEP_PLAIN,
+              const FirstTouch& first = FirstTouch{}) {
+  const RowCtx c = make_ctx(st, gi, row0, batch, s, first);
   const Group& g = *c.g;
   const int m = (int)g.m, n = (int)g.n, r = (int)g.r;
   if (c.ev) st->group_timed[gi] = 1;
@@ -1274,8 +1283,9 @@ int step_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, 
 //   always:   W = B V;  M <- B - (1-mu) W V^T;  X <- X - eta sqrt(m/n) ColNorm(W) V^T
 // ColNorm(W) V^T = W (V diag(d))^T with d_j = 1 / (||W_j|| + eps), so the fused update kernel of the Dion step
 // serves unchanged with A = W, B = V, B2 = V diag(d).
-int lazy_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, bool refresh, hipStream_t s) {
-  const RowCtx c = make_ctx(st, gi, row0, batch, s);
+int lazy_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, bool refresh, hipStream_t s,
+              const FirstTouch& first = FirstTouch{}) {
+  const RowCtx c = make_ctx(st, gi, row0, batch, s, first);
   const Group& g = *c.g;
   const int m = (int)g.m, n = (int)g.n, r = (int)g.r;
   if (c.ev) st->group_timed[gi] = 1;
@@ -1319,8 +1329,9 @@ int lazy_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, 
 //   X <- X - eta sqrt(m/n) Vt_new P'^T = X - eta sqrt(m/n) R' (P' diag(d))^T
 // i.e. the products of the standard step in the other order, the orthonormalisation on n x r, and the fused
 // update kernel with A = R', B = P', B2 = P' diag(d).
-int transposed_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, hipStream_t s) {
-  const RowCtx c = make_ctx(st, gi, row0, batch, s);
+int transposed_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, hipStream_t s,
+                    const FirstTouch& first = FirstTouch{}) {
+  const RowCtx c = make_ctx(st, gi, row0, batch, s, first);
   const Group& g = *c.g;
   const int m = (int)g.m, n = (int)g.n, r = (int)g.r;
   if (c.ev) st->group_timed[gi] = 1;
@@ -1349,6 +1360,28 @@ int transposed_rows(dion_state* st, int gi, int row0, int batch, float mu, float
   STAGECHK(mark(c, DION_STAGE_K5_UPDATE, 0));
   STAGECHK(stage_k5(c, SLOT_P16, SLOT_R16, SLOT_Q16, SLOT_Z, pt, scratch, mu, eta));
   STAGECHK(mark(c, DION_STAGE_K5_UPDATE, 1));
+  return DION_OK;
+}
+
+// The caller's addresses for a call on the one matrix in table row `row` of group gi: left to the call's first launch where that is
+// one that can take them (a product with M + G of the general core, the bf16 copy of M + G or of the factor, all on the
+// caller's stream), else written by a launch of their own.
+int begin_single(dion_state* st, int gi, int row, void* X, const void* G, void* M, void* Q, hipStream_t s, FirstTouch* first) {
+  const Group& g = st->groups[gi];
+  *first = FirstTouch{};
+  const RowCtx c = make_ctx(st, gi, row - g.first_row, 1, s, *first);
+  if (!g.big || (g.form == DION_FORM_STANDARD && k1_parts_mode(c) == K1_WHOLE)) {
+    first->user[SLOT_X] = X; first->user[SLOT_G] = const_cast<void*>(G); first->user[SLOT_M] = M; first->user[SLOT_Q] = Q;
+    first->row = st->table + (size_t)row * NSLOTS;
+    first->status = st->status + row;
+    first->counter = st->step_counter;
+    return DION_OK;
+  }
+  void* xs[1] = {X};
+  const void* gs[1] = {G};
+  void* ms[1] = {M};
+  void* qs[1] = {Q};
+  HIPCHK(launch_set_user_ptrs(st->table, NSLOTS, row, 1, xs, gs, ms, qs, s, st->status, st->step_counter));
   return DION_OK;
 }
 
@@ -1415,9 +1448,9 @@ int for_each_group(dion_state* st, hipStream_t s, F&& fn) {
   return rc;
 }
 
-int any_step_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, hipStream_t s) {
-  return st->groups[gi].form == DION_FORM_TRANSPOSED ? transposed_rows(st, gi, row0, batch, mu, eta, s)
-                                                     : step_rows(st, gi, row0, batch, mu, eta, s);
+int any_step_rows(dion_state* st, int gi, int row0, int batch, float mu, float eta, hipStream_t s, const FirstTouch& first = FirstTouch{}) {
+  return st->groups[gi].form == DION_FORM_TRANSPOSED ? transposed_rows(st, gi, row0, batch, mu, eta, s, first)
+                                                     : step_rows(st, gi, row0, batch, mu, eta, s, STEP_PLAIN, first);
 }
 
 bool aligned16(const void* p) { return p && ((uintptr_t)p & 15u) == 0; }
@@ -1570,12 +1603,9 @@ int dion_step(dion_state_t* st, void* X, const void* G, void* M, void* Q, int64_
   hipStream_t s = (hipStream_t)hip_stream;
   st->last_stream = s;
   std::fill(st->group_timed.begin(), st->group_timed.end(), 0);
-  void* xs[1] = {X};
-  const void* gs[1] = {G};
-  void* ms[1] = {M};
-  void* qs[1] = {Q};
-  HIPCHK(launch_set_user_ptrs(st->table, NSLOTS, e.row, 1, xs, gs, ms, qs, s, st->status, st->step_counter));
-  return any_step_rows(st, e.group, e.row - g.first_row, 1, mu, eta, s);
+  FirstTouch first;
+  STAGECHK(begin_single(st, e.group, e.row, X, G, M, Q, s, &first));
+  return any_step_rows(st, e.group, e.row - g.first_row, 1, mu, eta, s, first);
 }
 
 int dion_lazy_step_batched(dion_state_t* st, int count, void* const* X, const void* const* G, void* const* M, void* const* V,
@@ -1616,12 +1646,9 @@ int dion_lazy_step(dion_state_t* st, void* X, const void* G, void* M, void* V, i
   hipStream_t s = (hipStream_t)hip_stream;
   st->last_stream = s;
   std::fill(st->group_timed.begin(), st->group_timed.end(), 0);
-  void* xs[1] = {X};
-  const void* gs[1] = {G};
-  void* ms[1] = {M};
-  void* qs[1] = {V};
-  HIPCHK(launch_set_user_ptrs(st->table, NSLOTS, e.row, 1, xs, gs, ms, qs, s, st->status, st->step_counter));
-  return lazy_rows(st, e.group, e.row - g.first_row, 1, mu, eta, refresh != 0, s);
+  FirstTouch first;
+  STAGECHK(begin_single(st, e.group, e.row, X, G, M, V, s, &first));
+  return lazy_rows(st, e.group, e.row - g.first_row, 1, mu, eta, refresh != 0, s, first);
 }
 
 int dion_double_step(dion_state_t* st1, dion_state_t* st2, int count, void* const* X, const void* const* G, void* const* M1,

@@ -139,7 +139,7 @@ hipError_t launch_copy_gated(void* const* table, int nslots, int batch, int slot
                              hipStream_t s);
 // out16 = bf16(M + G) as [rows][cols]  (rows * cols a multiple of 8)
 hipError_t launch_sum_bf16(void* const* table, int nslots, int batch, int slot_m, int slot_g, bool gbf16, int slot_out16,
-                           long long rows, long long cols, hipStream_t s);
+                           long long rows, long long cols, hipStream_t s, FirstTouch first = FirstTouch{});
 // ... for the columns [col_first, col_first + col_count) (multiples of 8) of the rows [row_first, row_first + row_count) only
 hipError_t launch_sum_bf16_cols(void* const* table, int nslots, int batch, int slot_m, int slot_g, bool gbf16, int slot_out16,
                                 long long rows, long long cols, long long row_first, long long row_count, long long col_first,
@@ -179,7 +179,7 @@ hipError_t launch_split_bf16(void* const* table, int nslots, int batch, int slot
                              long long cols, int slot_hi, int slot_lo, int slot_hiT, int slot_loT, hipStream_t s,
                              int skip_slot = -1);   // skip_slot >= 0: nothing happens for matrices whose int32 there is non-zero
 hipError_t launch_convert_bf16(void* const* table, int nslots, int batch, int slot_in, int slot_out16, int slot_outT16,
-                               long long rows, long long cols, hipStream_t s, int skip_slot = -1);
+                               long long rows, long long cols, hipStream_t s, int skip_slot = -1, FirstTouch first = FirstTouch{});
 // Up to three matrices at once: fp32 [rows][cols] -> bf16 [rows_out][cols_out], zeros beyond (cols_out a multiple of 8)
 struct PadJob { int slot_in, slot_out; long long rows, rows_out; };
 hipError_t launch_pad_bf16(void* const* table, int nslots, int batch, const PadJob* jobs, int njobs, int cols, int cols_out, hipStream_t s);

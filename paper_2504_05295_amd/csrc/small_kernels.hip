@@ -516,10 +516,12 @@ hipError_t launch_scale_cols(void* const* table, int nslots, int batch, int slot
 // fp32 [rows][cols] -> bf16 [rows][cols] and / or bf16 [cols][rows], 64x64 tiles transposed through LDS.
 // skip_slot >= 0 and the int32 there non-zero: nothing to do.
 __global__ void __launch_bounds__(256) convert_bf16_kernel(void* const* table, int nslots, int slot_in, int slot_out16,
-                                                           int slot_outT16, long long rows, long long cols, int skip_slot) {
+                                                           int slot_outT16, long long rows, long long cols, int skip_slot,
+                                                           const FirstTouch first) {
   void* const* tab = table + (size_t)blockIdx.z * nslots;
+  first_touch(first, blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0);
   if (skip_slot >= 0 && *(const int*)tab[skip_slot] != 0) return;
-  const float* in = (const float*)tab[slot_in];
+  const float* in = (const float*)first_ptr(first, tab, slot_in);
   uint16_t* out16 = slot_out16 >= 0 ? (uint16_t*)tab[slot_out16] : nullptr;
   uint16_t* outT = slot_outT16 >= 0 ? (uint16_t*)tab[slot_outT16] : nullptr;
   __shared__ float tile[64][65];
@@ -545,10 +547,10 @@ __global__ void __launch_bounds__(256) convert_bf16_kernel(void* const* table, i
   }
 }
 hipError_t launch_convert_bf16(void* const* table, int nslots, int batch, int slot_in, int slot_out16, int slot_outT16,
-                               long long rows, long long cols, hipStream_t s, int skip_slot) {
+                               long long rows, long long cols, hipStream_t s, int skip_slot, FirstTouch first) {
   if (rows % 64 || cols % 64) return hipErrorInvalidValue;
   hipLaunchKernelGGL(convert_bf16_kernel, dim3((unsigned)(cols / 64), (unsigned)(rows / 64), batch), dim3(256), 0, s, table, nslots,
-                     slot_in, slot_out16, slot_outT16, rows, cols, skip_slot);
+                     slot_in, slot_out16, slot_outT16, rows, cols, skip_slot, first);
   return hipGetLastError();
 }
 
@@ -558,10 +560,11 @@ hipError_t launch_convert_bf16(void* const* table, int nslots, int batch, int sl
 // through LDS.
 template <bool GBF16>
 __global__ void __launch_bounds__(256) sum_bf16_stream_kernel(void* const* table, int nslots, int slot_m, int slot_g, int slot_out16,
-                                                              long long count8) {
+                                                              long long count8, const FirstTouch first) {
   void* const* tab = table + (size_t)blockIdx.y * nslots;
-  const f32x4_t* M = (const f32x4_t*)tab[slot_m];
-  const void* G = tab[slot_g];
+  first_touch(first, blockIdx.x == 0 && blockIdx.y == 0);
+  const f32x4_t* M = (const f32x4_t*)first_ptr(first, tab, slot_m);
+  const void* G = first_ptr(first, tab, slot_g);
   u32x4_t* out = (u32x4_t*)tab[slot_out16];
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count8; i += stride) {
@@ -621,15 +624,15 @@ hipError_t launch_sum_bf16_cols(void* const* table, int nslots, int batch, int s
   return hipGetLastError();
 }
 hipError_t launch_sum_bf16(void* const* table, int nslots, int batch, int slot_m, int slot_g, bool gbf16, int slot_out16,
-                           long long rows, long long cols, hipStream_t s) {
+                           long long rows, long long cols, hipStream_t s, FirstTouch first) {
   if (rows * cols % 8 || batch > 65535 || batch < 1) return hipErrorInvalidValue;
   const long long count8 = rows * cols / 8;
   long long blocks = (count8 + 255) / 256;
   const long long cap = 256LL * 64 / (batch < 64 ? batch : 64) + 1;   // about 64 workgroups per compute unit over the whole launch
   if (blocks > cap) blocks = cap;
   const dim3 grid((unsigned)blocks, batch);
-  if (gbf16) hipLaunchKernelGGL(sum_bf16_stream_kernel<true>, grid, dim3(256), 0, s, table, nslots, slot_m, slot_g, slot_out16, count8);
-  else hipLaunchKernelGGL(sum_bf16_stream_kernel<false>, grid, dim3(256), 0, s, table, nslots, slot_m, slot_g, slot_out16, count8);
+  if (gbf16) hipLaunchKernelGGL(sum_bf16_stream_kernel<true>, grid, dim3(256), 0, s, table, nslots, slot_m, slot_g, slot_out16, count8, first);
+  else hipLaunchKernelGGL(sum_bf16_stream_kernel<false>, grid, dim3(256), 0, s, table, nslots, slot_m, slot_g, slot_out16, count8, first);
   return hipGetLastError();
 }
 
