@@ -1118,7 +1118,9 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
     const u64 v = flag_load(x.lflag + row);
     return (unsigned)(v >> 32) == (unsigned)x.epoch && (unsigned)v >= (unsigned)cols;
   };
-  // ---- the inverse (FUSE_INV)
+  // ---- the inverse (FUSE_INV), in bf16 mode split into its halves, too: the triangular product reads those
+  uint16_t* const wh = p.wh ? p.wh + 2 * mat : nullptr;
+  uint16_t* const wl = p.wl + 2 * mat;
   auto w_ready = [&](int p_, int e) __attribute__((always_inline)) {   // tile (p_, e) of W is final
     return e == p_ ? flag_load32(w11_flag(p_)) == ep : flag_load(vflag + p_ * nb + e) == x.epoch;
   };
@@ -1172,6 +1174,32 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       barrier();   // everybody's stores have completed
       if (t == 0) flag_store(vflag + p_ * nb + e, x.epoch);
+      if (wh) {   // (behind the flag: nobody in this launch waits for them)
+        const long long at = (long long)(p_ * CB + frow) * ld + e * CB + fcol;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const long long o = at + (8 * (v / 4) + (v % 4)) * ld;
+          const uint32_t h = pack_bf16x2(res[v], 0.f);
+          gstore<uint16_t>(wh + o, (uint16_t)h);
+          gstore<uint16_t>(wl + o, (uint16_t)pack_bf16x2(res[v] - bf16_lo(h), 0.f));
+        }
+      }
+    }
+    return true;
+  };
+  // the halves of W11(p_), by one team
+  auto w_diag = [&](int p_) __attribute__((always_inline)) -> bool {
+    if (!wh || p_ % pr != a || p_ % pc != b) return true;   // (uniform)
+    if (!wait_team(t == 0, [&] { return flag_load32(w11_flag(p_)) == ep; })) return false;
+    tile_regs w;
+    tile_to_regs(w, tile_at(x.W, p_, p_), ld, t);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const long long o = (long long)(p_ * CB + (t >> 4) + 16 * q) * ld + p_ * CB + (t & 15) * 4;
+      const f32x4_t f = w.v[q];
+      const uint32_t h01 = pack_bf16x2(f[0], f[1]), h23 = pack_bf16x2(f[2], f[3]);
+      gstore<u32x2_t>(wh + o, u32x2_t{h01, h23});
+      gstore<u32x2_t>(wl + o, u32x2_t{pack_bf16x2(f[0] - bf16_lo(h01), f[1] - bf16_hi(h01)), pack_bf16x2(f[2] - bf16_lo(h23), f[3] - bf16_hi(h23))});
     }
     return true;
   };
@@ -1243,6 +1271,7 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
     // the previous panel and this one's look-ahead work), then this team's part of row p_
     if (FUSE_INV && p_ >= 1 && !w_rest(p_ - 1)) return;
     if (FUSE_INV && !w_row(p_)) return;
+    if (FUSE_INV && !w_diag(p_)) return;
     // the tiles of L that this team's other updates of panel p_ need: one thread per block row (a superset)
     {
       const bool need = t > p_ && t < nb && reads_row;
@@ -1254,7 +1283,7 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
     for (int j = b + ((p_ + 1 - b + pc - 1) / pc) * pc; j < nb; j += pc)
       for (int i = a + ((j + 3 - a + pr - 1) / pr) * pr; i < nb; i += pr) update(i, j, p_);
   }
-  if (FUSE_INV) w_row(nb - 1);   // (row nb - 2 of W has no rows from nb down to go into)
+  if (FUSE_INV && w_row(nb - 1)) w_diag(nb - 1);   // (row nb - 2 of W has no rows from nb down to go into)
 }
 
 hipError_t launch_chol_stream(CholStreamArgs p, int batch, hipStream_t s) {

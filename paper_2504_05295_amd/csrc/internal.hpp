@@ -250,6 +250,9 @@ struct CholStreamArgs {
   int chain;               // 1: one more workgroup, number 0, carries the whole chain of diagonal blocks (pr x pc helpers)
   int vflag_off;           // chain only: > 0: the helpers form W = L^-1 as well (no inverse pass afterwards), and (rp / 64)^2
                            // flag words for it start this many 64-bit words into the matrix' sync array; 0: they do not
+  // vflag_off > 0: W also goes here split as hi + lo (bf16, rp x rp each, 2 * stride apart), on and below the block diagonal; or null
+  uint16_t* wh = nullptr;
+  uint16_t* wl = nullptr;
   // An adaptive pass (tau2 > 0) takes launch_first_order_inverse's decision for tau = sqrt(tau2) in here, from the partial
   // sums of its defect kernel, leaves it in fast and, when it is set, does that kernel's work instead of its own.
   const float* defect = nullptr;   // (`stride` words between the matrices of a batch, as fast)
