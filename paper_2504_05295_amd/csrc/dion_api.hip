@@ -108,8 +108,8 @@ struct Group {
                       // 256 x 256 tiles (or, one matrix, with parts of them) and the copy fits the kernels' 32-bit offsets
   bool big;           // the large-tile bf16 kernels serve this group (bf16 operand mode, tile-aligned shape): only then
                       // are the bf16 operand copies carved
-  bool w_halves;      // big, and SLOT_WH16 / SLOT_WL16 are zero above the block diagonal from init on (not in the state that is made
-                      // by every call of the static entry point): a factorisation may leave the halves of its inverse there
+  bool w_halves;      // big, and SLOT_WH16 / SLOT_WL16 are zero above the block diagonal from init on (not in the static entry point's
+                      // workspace, which calls of all shapes share): a factorisation may leave the halves of its inverse there
   bool k5_direct;     // not big, but bf16 operands and large enough for the update to run on the direct-load core all the same, on
                       // padded bf16 copies of the factors
   size_t bytes_per_entry;
@@ -190,7 +190,11 @@ bool plan_k5_direct(const Group& g) {
   return tiles >= 144 && (tiles >= 256 || g.r >= 80) && mp < (1ll << 31) && np < (1ll << 31) && std::max(mp, np) * g.rp * 2 < (1ll << 32) &&
          3ll * g.count <= 65535;
 }
-// lean: nothing that takes workspace only for speed (splits of the products off the large-tile path)
+// What a plan takes of workspace only for speed: all of it; all but the padded copies of the ragged update; nothing (no splits of the
+// products off the large-tile path either).  A workspace that is too small for one takes the next: of a state the second at most,
+// of the static entry point the third.
+enum class Scratch { full, no_copies, lean };
+
 void plan_gram(Group& g, bool lean) {
   g.k1 = plan_product(g.m, g.r, g.n, g.count, !lean && !g.big);
   g.k2 = plan_product(g.n, g.r, g.m, g.count, !lean && !g.big);
@@ -288,7 +292,7 @@ bool shapes_ok(int count, const int64_t* m, const int64_t* n, const int64_t* r) 
 }
 
 bool build_plan(int count, const int64_t* m, const int64_t* n, const int64_t* r, const int* form, int math,
-                std::vector<Entry>& entries, std::vector<Group>& groups, bool lean = false) {
+                std::vector<Entry>& entries, std::vector<Group>& groups, Scratch scratch = Scratch::full) {
   entries.resize(count);
   groups.clear();
   for (int i = 0; i < count; ++i) {
@@ -315,9 +319,9 @@ bool build_plan(int count, const int64_t* m, const int64_t* n, const int64_t* r,
   for (auto& g : groups) {
     g.first_row = row;
     row += g.count;
-    plan_gram(g, lean);
-    g.w_halves = g.big && !lean;
-    g.k5_direct = !g.big && !lean && math == DION_MATH_BF16 && plan_k5_direct(g);
+    plan_gram(g, scratch == Scratch::lean);
+    g.w_halves = g.big;
+    g.k5_direct = !g.big && scratch == Scratch::full && math == DION_MATH_BF16 && plan_k5_direct(g);
     g.carve = carve_entry(g);
     g.bytes_per_entry = g.carve.total;
   }
@@ -400,9 +404,9 @@ void create_side_stream(dion_state* st) {
 // (M_dev / Q_dev may be null: those two slots are refreshed by every step anyway).  Touches no device memory.
 int plan_state(dion_state* st, int count, const int64_t* m, const int64_t* n, const int64_t* r, const int* form, int g_dtype,
                int math, void* workspace_dev, size_t workspace_bytes, void* const* M_dev, void* const* Q_dev,
-               std::vector<void*>& host, bool lean = false) {
+               std::vector<void*>& host, Scratch scratch) {
   st->count = count; st->g_dtype = g_dtype; st->math = math;
-  build_plan(count, m, n, r, form, math, st->entries, st->groups, lean);
+  build_plan(count, m, n, r, form, math, st->entries, st->groups, scratch);
   st->ws = (char*)workspace_dev;
   st->ws_bytes = workspace_bytes;
   st->table = (void**)st->ws;
@@ -1430,8 +1434,8 @@ void create_group_streams(dion_state* st) {
 // overlap) group gi goes to the caller's stream or one of the state's in turn; these start behind what the caller's stream
 // holds so far, and it goes on behind them, whether or not a group failed to enqueue.  Nothing but the pointer table and the
 // step counter, written before this, is shared between groups.  Two layers of d = 768, r = 192 (three groups of about 200 us
-// each, nearly all of it launches and kernels of a few workgroups): 616 us one after the other, 386 us so, when steps follow one
-// another and the host is a step ahead; a step that finds the queue empty, where a group's launches start only when the host has
+// each, nearly all of it launches and kernels of a few workgroups): 616 us one after the other, 386 us so (346 with today's
+// factorisation), when steps follow one another and the host is a step ahead; a step that finds the queue empty, where a group's launches start only when the host has
 // enqueued the groups before it, 666 and 457-510 us.
 template <class F>
 int for_each_group(dion_state* st, hipStream_t s, F&& fn) {
@@ -1477,11 +1481,11 @@ bool batch_args_ok(const dion_state* st, int count, void* const* X, const void* 
   return true;
 }
 
-int workspace_need(int count, const int64_t* m, const int64_t* n, const int64_t* r, int math, bool lean, size_t* bytes_out) {
+int workspace_need(int count, const int64_t* m, const int64_t* n, const int64_t* r, int math, Scratch scratch, size_t* bytes_out) {
   try {
     std::vector<Entry> entries;
     std::vector<Group> groups;
-    build_plan(count, m, n, r, nullptr, math, entries, groups, lean);   // the form does not change any size
+    build_plan(count, m, n, r, nullptr, math, entries, groups, scratch);   // the form does not change any size
     size_t total = header_bytes(count);
     for (auto& g : groups) total += g.bytes_per_entry * g.count;
     *bytes_out = total + 256;
@@ -1499,7 +1503,7 @@ int dion_workspace_bytes(int count, const int64_t* m, const int64_t* n, const in
                          size_t* bytes_out) {
   if (!bytes_out || !shapes_ok(count, m, n, r)) return DION_EINVAL;
   if ((g_dtype != DION_G_F32 && g_dtype != DION_G_BF16) || (math != DION_MATH_F32 && math != DION_MATH_BF16)) return DION_EINVAL;
-  return workspace_need(count, m, n, r, math, false, bytes_out);
+  return workspace_need(count, m, n, r, math, Scratch::full, bytes_out);
 }
 
 int dion_init_state(dion_state_t** out, int count, const int64_t* m, const int64_t* n, const int64_t* r, int g_dtype,
@@ -1522,7 +1526,13 @@ int dion_init_state_ex(dion_state_t** out, int count, const int64_t* m, const in
   if (rc != DION_OK) return rc;
   if (count > 0 && (!M_dev || !Q_dev)) return DION_EINVAL;
   if (!workspace_dev || ((uintptr_t)workspace_dev & 255u)) return DION_EINVAL;
-  if (workspace_bytes < need) return DION_EWORKSPACE;
+  Scratch scratch = Scratch::full;
+  if (workspace_bytes < need) {
+    scratch = Scratch::no_copies;
+    rc = workspace_need(count, m, n, r, math, scratch, &need);
+    if (rc != DION_OK) return rc;
+    if (workspace_bytes < need) return DION_EWORKSPACE;
+  }
   for (int i = 0; i < count; ++i)
     if (!aligned16(M_dev[i]) || !aligned16(Q_dev[i])) return DION_EINVAL;
   hipStream_t s = (hipStream_t)hip_stream;
@@ -1533,7 +1543,7 @@ int dion_init_state_ex(dion_state_t** out, int count, const int64_t* m, const in
   try {
     st = new dion_state();
     std::vector<void*> host;
-    const int prc = plan_state(st, count, m, n, r, form, g_dtype, math, workspace_dev, workspace_bytes, M_dev, Q_dev, host);
+    const int prc = plan_state(st, count, m, n, r, form, g_dtype, math, workspace_dev, workspace_bytes, M_dev, Q_dev, host, scratch);
     if (prc != DION_OK) {
       delete st;
       return prc;
@@ -1901,13 +1911,15 @@ extern "C" int dion_step_static(void* X, const void* G, void* M, void* Q, int64_
   size_t need = 0;
   int rc = dion_workspace_bytes(1, &m, &n, &r, g_dtype, math, &need);   // validates the shape and the two type codes
   if (rc != DION_OK) return rc;
-  // a shape whose plan is too large for the static workspace runs on the lean one; what that does not fit either is refused
-  const bool lean = need > kStaticScratchBytes;
-  if (lean) {
-    rc = workspace_need(1, &m, &n, &r, math, true, &need);
+  // a shape whose plan is too large for the static workspace runs on the next smaller one; what the lean one does not fit is refused
+  Scratch room = Scratch::full;
+  for (Scratch next : {Scratch::no_copies, Scratch::lean}) {
+    if (need <= kStaticScratchBytes) break;
+    room = next;
+    rc = workspace_need(1, &m, &n, &r, math, room, &need);
     if (rc != DION_OK) return rc;
-    if (need > kStaticScratchBytes) return DION_EWORKSPACE;
   }
+  if (need > kStaticScratchBytes) return DION_EWORKSPACE;
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
   if (dev < 0 || dev >= 16) return DION_EINVAL;
@@ -1929,7 +1941,8 @@ extern "C" int dion_step_static(void* X, const void* G, void* M, void* Q, int64_
     try {
       st = new dion_state();
       std::vector<void*> host;
-      rc = plan_state(st, 1, &m, &n, &r, nullptr, g_dtype, math, slot.ptr, kStaticScratchBytes, nullptr, nullptr, host, lean);
+      rc = plan_state(st, 1, &m, &n, &r, nullptr, g_dtype, math, slot.ptr, kStaticScratchBytes, nullptr, nullptr, host, room);
+      if (rc == DION_OK) st->groups[0].w_halves = false;   // (what an earlier call left there is not zero, and clearing it is another launch)
       if (rc == DION_OK && launch_set_table_row(st->table, host.data(), s) != hipSuccess) rc = DION_ELAUNCH;
     } catch (const std::bad_alloc&) {
       rc = DION_ENOMEM;
