@@ -176,19 +176,29 @@ GramPlan plan_gram_rows(const Group& g, int64_t rows) {
 long long round_up(long long x, long long q) { return (x + q - 1) / q * q; }
 // The update of bf16 mode off the large-tile path.  The general core forms it from the fp32 factors, rounding them on the way to
 // the LDS, on tiles of 128 x 64: 2.6 times as many operand bytes as bytes of M, X and G.  The direct-load core's 256 x 128 tile
-// on bf16 copies, padded to whole tiles by a launch more (5-8 us), moves a third as many.  us a step, general core / direct-load:
-//   tiles of 256 x 128 (one matrix)
-//   32-96    1111 x 1733 r = 139  150 / 163;  1500 x 1500 r = 250  169 / 177;  2001 x 1501 r = 300  202 / 207
-//   128      2048 x 2048 r = 200  173 / 177
-//   153-216  2050 x 2050 r = 400  274 / 262;  2049 x 2304 r = 250  196 / 190;  2304 x 2304 r = 100  144 / 143;  9001 x 700 r = 100
-//            188 / 183;  3000 x 2048 r = 64  116 / 117;  16001 x 300 r = 50  192 / 194
-//   256-     3001 x 3001 r = 500  404 / 378;  5003 x 2999 r = 375  429 / 384;  4001 x 4003 r = 20  211 / 202;  8192 x 8192 r = 100
-//            647 / 622;  10001 x 10003 r = 300  2476 / 2267;  Lazy-Dion 5003 x 2999 r = 375  211 / 167
-// A batch of small matrices loses as one alone does (512 x 512 and 512 x 2048, r = 100, eight layers 350 / 403): judged per matrix.
+// on bf16 copies, padded to whole tiles by a launch more (5-8 us), moves a third as many.  It loses where the contraction is short
+// (the general core's extra bytes grow with r), where the last round of 256 tiles is much padding or nearly empty, and where there
+// are few tiles and the last columns, one by one (n % 4), lie on each one's way.  Lazy-Dion without refresh, whose update is most
+// of it, us a step, general core / direct-load:
+//   one round or a part    5120 x 1111 r = 100, 200  70 / 76, 86 / 87;  3000 x 2047 r = 72, 200  70 / 75, 93 / 97;  2500 x 2500 r = 200
+//                          85 / 82;  2100 x 2100 r = 200  77 / 67;  9001 x 700 r = 200  102 / 94;  300 x 16001 r = 200  95 / 96
+//   two, the last empty    66000 x 127 r = 72  99 / 129;  127 x 40000 r = 72  103 / 132;  3001 x 3001 r = 72, 200  104 / 107, 127 / 124
+//   two or three           5003 x 2999 r = 64, 128, 375  130 / 128, 152 / 145, 211 / 167;  4097 x 4095 r = 72, 200  155 / 163, 197 / 196
+//   five and more          8191 x 4097 r = 72, 100, 200  264 / 251, 282 / 254, 346 / 302
+//                          16383 x 2047 r = 80  264 / 275;  1031 x 40001 r = 72  384 / 389
+//   r = 256                6000 x 2303  172 / 179;  5003 x 2999  192 / 180;  4100 x 4100  212 / 199;  20001 x 703  229 / 215
+// Whole steps: 5003 x 2999 r = 375 429 / 384;  7001 x 5001 r = 600 1343 / 1199;  10001 x 10003 r = 300 2476 / 2267.  So: two rounds'
+// worth of tiles from r = 256 on (352 with two or three last columns), four rounds' from r = 72 on if neither side is narrow, two
+// thirds of the rounds used.  A
+// batch of small matrices loses as one alone does (512 x 512 and 512 x 2048, r = 100, eight layers 350 / 403): judged per matrix.
+// (The last four columns loaded together and shifted into place, all lanes alike: 5120 x 1111 r = 200 87 -> 84, but 8191 x 4097
+// r = 200 302 -> 311, 5003 x 2999 r = 375 step 440 -> 449: not kept.)
 bool plan_k5_direct(const Group& g) {
   const long long mp = round_up(g.m, 256), np = round_up(g.n, 128), tiles = (mp / 256) * (np / 128);
-  return tiles >= 144 && (tiles >= 256 || g.r >= 80) && mp < (1ll << 31) && np < (1ll << 31) && std::max(mp, np) * g.rp * 2 < (1ll << 32) &&
-         3ll * g.count <= 65535;
+  const long long round_area = 256ll * 256 * 128, rounds = (tiles + 255) / 256;
+  const bool enough = tiles >= 1024 && std::min(g.m, g.n) >= 4096 && g.n % 4 < 2 ? g.r >= 72 : tiles >= 400 && g.r >= (g.n % 4 < 2 ? 256 : 352);
+  return enough && 3.0 * (double)g.m * (double)g.n >= 2.0 * (double)(rounds * round_area) && mp < (1ll << 31) && np < (1ll << 31) &&
+         std::max(mp, np) * g.rp * 2 < (1ll << 32) && 3ll * g.count <= 65535;
 }
 // What a plan takes of workspace only for speed: all of it; all but the padded copies of the ragged update; nothing (no splits of the
 // products off the large-tile path either).  A workspace that is too small for one takes the next: of a state the second at most,

@@ -16,7 +16,7 @@ def up(x, k):
 def test_state_without_room_for_the_copies():
     import torch
     from paper_2504_05295_amd import binding as B
-    m, n, r = 2305, 2307, 90
+    m, n, r = 5003, 2999, 360
     gp = GpuProblem([(m, n, r)], True, "bf16", seed=11)
     need = B.dion_workspace_bytes([(m, n, r)], B.DION_G_BF16, B.DION_MATH_BF16)
     copies = 2 * up(r, 64) * (up(m, 256) + 2 * up(n, 128))
@@ -33,7 +33,7 @@ def test_state_without_room_for_the_copies():
         assert gp.step(MU, ETA) == (0, -1)
         B.dion_step(st, X, gp.G[0], M, Q, MU, ETA)
         torch.cuda.synchronize()
-        # the same bf16 factors, 90 products of which are summed in fp32 in another order; a difference of 1e-6 in M may move a
+        # the same bf16 factors, 360 products of which are summed in fp32 in another order; a difference of 1e-6 in M may move a
         # bf16 operand of the next step by one place, 2^-9, in few of its elements
         tol = 1e-5 if t == 0 else 2e-3
         for u, v in ((X, gp.X[0]), (M, gp.M[0]), (Q, gp.Q[0])):
