@@ -93,32 +93,87 @@ __device__ __forceinline__ void spread(float (&a)[16], const f32x4_t& T) {
   }
 }
 
-// One column of an elimination: a[k] += f a_j of lane k for k > j, w[v] += f w[v] of lane j, "of lane" within the row of
-// sixteen.  The broadcast is the multiply-add's own data-parallel operand, which the compiler would leave as a move in front of
-// it, twice the instructions; hence by hand.  A register written by a vector instruction may be such an operand two instructions
-// later at the earliest, and nobody checks that here: a[j + 1], which the next column reads first, is written first, with
-// the four updates of w behind it in the same statement; everything else a column reads through the broadcast
-// was written before that column's f, which depends on a[j], or, w, four instructions before.
-#define DION_FMAC_BCAST(D, S, LANE) "v_fmac_f32_dpp " D ", " S ", %[f] row_newbcast:" LANE " row_mask:0xf bank_mask:0xf\n\t"
-template <int K>
-__device__ __forceinline__ void fmac_bcast(float& d, float x, float f) {
-  asm(DION_FMAC_BCAST("%[d]", "%[x]", "%[k]") : [d] "+v"(d) : [x] "v"(x), [f] "v"(f), [k] "n"(K));
-}
-template <int J>
-__device__ __forceinline__ void column(float (&a)[16], f32x4_t& w, float f) {
-  const float aj = a[J];
-  if constexpr (J < 15) {   // (column 15 has no rows below it)
-    float next = a[J + 1], w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
-    asm(DION_FMAC_BCAST("%[n]", "%[a]", "%[k]") DION_FMAC_BCAST("%[w0]", "%[w0]", "%[j]") DION_FMAC_BCAST("%[w1]", "%[w1]", "%[j]")
-            DION_FMAC_BCAST("%[w2]", "%[w2]", "%[j]") DION_FMAC_BCAST("%[w3]", "%[w3]", "%[j]")
-        : [n] "+v"(next), [w0] "+v"(w0), [w1] "+v"(w1), [w2] "+v"(w2), [w3] "+v"(w3)
-        : [a] "v"(aj), [f] "v"(f), [j] "n"(J), [k] "n"(J + 1));
-    a[J + 1] = next;
-    w = f32x4_t{w0, w1, w2, w3};
+// One column of an elimination: a[k] += f a_j of lane k for k > j, w[v] += f w[v] of lane j, "of lane" within the row of sixteen,
+// and the next column's pivot and its reciprocal.  f: 0 in the lanes up to j, else -a_j / pivot; without RANK it comes as a_j and
+// is multiplied here.  The broadcast is the multiply-add's own data-parallel operand, which the compiler would leave as
+// a move in front of it, twice the instructions; hence by hand.
+// A register that a vector instruction writes may be such an operand only with two other instructions or wait states in
+// between.  The hardware does not check that; the compiler does, for its own instructions only, and it may put a copy of
+// any operand right in front of a statement.  So it holds inside the statement, whatever stands before it: a whole column is
+// one statement, that begins with two wait states, and behind a[j + 1], which the next pivot's broadcast reads, come two
+// other instructions.  (Without RANK the first wait state is also the one that the product needs behind the reciprocal, and the
+// product is the second.)
+#define DION_BCAST(OP, D, S, LANE) OP " " D ", " S " row_newbcast:" #LANE " row_mask:0xf bank_mask:0xf\n\t"
+#define DION_A(J, K) DION_BCAST("v_fmac_f32_dpp", "%[a" #K "]", "%[a" #J "], %[f]", K)
+#define DION_W(J, V) DION_BCAST("v_fmac_f32_dpp", "%[w" #V "]", "%[w" #V "], %[f]", J)
+#define DION_FROM_15(J) DION_A(J, 15)
+#define DION_FROM_14(J) DION_A(J, 14) DION_FROM_15(J)
+#define DION_FROM_13(J) DION_A(J, 13) DION_FROM_14(J)
+#define DION_FROM_12(J) DION_A(J, 12) DION_FROM_13(J)
+#define DION_FROM_11(J) DION_A(J, 11) DION_FROM_12(J)
+#define DION_FROM_10(J) DION_A(J, 10) DION_FROM_11(J)
+#define DION_FROM_9(J) DION_A(J, 9) DION_FROM_10(J)
+#define DION_FROM_8(J) DION_A(J, 8) DION_FROM_9(J)
+#define DION_FROM_7(J) DION_A(J, 7) DION_FROM_8(J)
+#define DION_FROM_6(J) DION_A(J, 6) DION_FROM_7(J)
+#define DION_FROM_5(J) DION_A(J, 5) DION_FROM_6(J)
+#define DION_FROM_4(J) DION_A(J, 4) DION_FROM_5(J)
+#define DION_FROM_3(J) DION_A(J, 3) DION_FROM_4(J)
+#define DION_FROM_2(J) DION_A(J, 2) DION_FROM_3(J)
+#define DION_RCP "v_rcp_f32 %[rcp], %[piv]\n\t"
+#define DION_CHAIN(J, K)                                                                                                      \
+  DION_A(J, K) DION_W(J, 0) DION_W(J, 1) DION_BCAST("v_mov_b32_dpp", "%[piv]", "%[a" #K "]", K) DION_W(J, 2) DION_W(J, 3)
+#define DION_OPERANDS                                                                                                         \
+  [a0] "+v"(a[0]), [a1] "+v"(a[1]), [a2] "+v"(a[2]), [a3] "+v"(a[3]), [a4] "+v"(a[4]), [a5] "+v"(a[5]), [a6] "+v"(a[6]),      \
+      [a7] "+v"(a[7]), [a8] "+v"(a[8]), [a9] "+v"(a[9]), [a10] "+v"(a[10]), [a11] "+v"(a[11]), [a12] "+v"(a[12]),             \
+      [a13] "+v"(a[13]), [a14] "+v"(a[14]), [a15] "+v"(a[15]), [w0] "+v"(w0), [w1] "+v"(w1), [w2] "+v"(w2), [w3] "+v"(w3),    \
+      [f] "+v"(f), [piv] "=&v"(piv), [rcp] "+v"(rcp)
+#define DION_COLUMN(J, K, REST)                                                                                               \
+  if constexpr (COL == J) {                                                                                                   \
+    if constexpr (RANK) asm("s_nop 1\n\t" DION_CHAIN(J, K) REST : DION_OPERANDS);                                             \
+    else asm("s_nop 0\n\tv_mul_f32_e64 %[f], -%[f], %[rcp]\n\t" DION_CHAIN(J, K) REST : DION_OPERANDS);                       \
   }
-  static_for<J + 2, 16>([&](auto kc) __attribute__((always_inline)) { fmac_bcast<decltype(kc)::value>(a[decltype(kc)::value], aj, f); });
+template <bool RANK, int COL>
+__device__ __forceinline__ void column(float (&a)[16], f32x4_t& w, float f, float& piv, float& rcp) {
+  float w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
+  DION_COLUMN(0, 1, DION_RCP DION_FROM_2(0))
+  DION_COLUMN(1, 2, DION_RCP DION_FROM_3(1))
+  DION_COLUMN(2, 3, DION_RCP DION_FROM_4(2))
+  DION_COLUMN(3, 4, DION_RCP DION_FROM_5(3))
+  DION_COLUMN(4, 5, DION_RCP DION_FROM_6(4))
+  DION_COLUMN(5, 6, DION_RCP DION_FROM_7(5))
+  DION_COLUMN(6, 7, DION_RCP DION_FROM_8(6))
+  DION_COLUMN(7, 8, DION_RCP DION_FROM_9(7))
+  DION_COLUMN(8, 9, DION_RCP DION_FROM_10(8))
+  DION_COLUMN(9, 10, DION_RCP DION_FROM_11(9))
+  DION_COLUMN(10, 11, DION_RCP DION_FROM_12(10))
+  DION_COLUMN(11, 12, DION_RCP DION_FROM_13(11))
+  DION_COLUMN(12, 13, DION_RCP DION_FROM_14(12))
+  DION_COLUMN(13, 14, DION_RCP DION_FROM_15(13))
+  DION_COLUMN(14, 15, "")
+  w = f32x4_t{w0, w1, w2, w3};   // (column 15 has no rows below it)
 }
-#undef DION_FMAC_BCAST
+#undef DION_BCAST
+#undef DION_A
+#undef DION_W
+#undef DION_FROM_15
+#undef DION_FROM_14
+#undef DION_FROM_13
+#undef DION_FROM_12
+#undef DION_FROM_11
+#undef DION_FROM_10
+#undef DION_FROM_9
+#undef DION_FROM_8
+#undef DION_FROM_7
+#undef DION_FROM_6
+#undef DION_FROM_5
+#undef DION_FROM_4
+#undef DION_FROM_3
+#undef DION_FROM_2
+#undef DION_RCP
+#undef DION_CHAIN
+#undef DION_OPERANDS
+#undef DION_COLUMN
 
 typedef __attribute__((address_space(3))) volatile int lds_counter;
 enum { W_DONE = 0, T_DONE, L_DONE, SUM_DONE, COUNTERS };   // all zero when a block starts
@@ -172,15 +227,17 @@ __device__ __forceinline__ void chain_wave(lds_float* S, lds_counter* sync, int 
     float a[16];
     spread(a, diag);
     f32x4_t w = one;
-    float piv_lane = 0.f;
+    float piv_lane = 0.f, piv = row_bcast<0>(a[0]), rcp = __builtin_amdgcn_rcpf(piv);
     static_for<0, 16>([&](auto jc) __attribute__((always_inline)) {
       constexpr int j = decltype(jc)::value;
-      const float piv = row_bcast<j>(a[j]);
-      const float below = c > j ? a[j] : 0.f;
-      float f = -below * __builtin_amdgcn_rcpf(piv);
-      if constexpr (RANK) f = piv > row_bcast<j>(thr_row[s]) ? f : 0.f;
-      column<j>(a, w, f);
-      piv_lane = c == j ? piv : piv_lane;
+      const float piv_j = piv;
+      float f = c > j ? a[j] : 0.f;
+      if constexpr (RANK) {
+        f = -f * rcp;
+        f = piv > row_bcast<j>(thr_row[s]) ? f : 0.f;
+      }
+      column<RANK, j>(a, w, f, piv, rcp);
+      piv_lane = c == j ? piv_j : piv_lane;
       if constexpr (j == 11 && s < 3) {
         // (s = 0: update_wave has the block in its registers, tile (0, 0) may be written; else the next step's tiles,
         // whose reads are in flight across the last columns)
