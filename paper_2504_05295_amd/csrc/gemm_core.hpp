@@ -84,6 +84,9 @@ __device__ __forceinline__ void* first_ptr(const FirstTouch& f, void* const* tab
   if (f.row == nullptr || slot > 3) return tab[slot];
   return slot == 0 ? f.user[0] : slot == 1 ? f.user[1] : slot == 2 ? f.user[2] : f.user[3];
 }
+// (Behind the kernel's last read of the table: a store in front of one makes it a vector load, for the compiler no longer knows that
+// the table is constant, and every base address a vector register pair.  In fp32 the 128 x 128 tile of (M + G)^T P took 170
+// registers so instead of 166, two waves per SIMD instead of three: two of 4096 x 4096, r = 1536, 1184 us instead of 900.)
 __device__ __forceinline__ void first_touch(const FirstTouch& f, bool first_workgroup) {
   if (f.row == nullptr || !first_workgroup || threadIdx.x != 0) return;
 #pragma unroll
@@ -391,7 +394,6 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::BM * Cfg::BN > 64 * 64 ? 2 : 3) 
   if (g.status_slot >= 0 && *(const int*)tab[g.status_slot] != 0) return;
 
   constexpr bool ASUM = ASRC == SRC_SUM_KC || ASRC == SRC_SUM_KS;
-  if constexpr (ASUM) first_touch(g.first, blockIdx.x == 0);
   auto ptr = [&](int slot) { return ASUM ? first_ptr(g.first, tab, slot) : tab[slot]; };
   const float* A0 = (const float*)ptr(g.A.slot0) + g.A.off + sub * g.A.sub_stride;
   const float* B0 = (const float*)ptr(g.B.slot0) + g.B.off + sub * g.B.sub_stride;
@@ -404,6 +406,12 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::BM * Cfg::BN > 64 * 64 ? 2 : 3) 
   if constexpr (BSRC == SRC_SUM_KC || BSRC == SRC_SUM_KS) {
     const long long o = g.B.off + sub * g.B.sub_stride;
     B1 = GBF16 ? (const void*)((const uint16_t*)tab[g.B.slot1] + o) : (const void*)((const float*)tab[g.B.slot1] + o);
+  }
+  void* out = nullptr;
+  if constexpr (ASUM) {
+    static_assert(EPI == EPI_STORE, "the table is not read again");
+    out = tab[g.E.slot];
+    first_touch(g.first, blockIdx.x == 0);
   }
   const float* B20 = nullptr;
   if constexpr (DUAL) B20 = (const float*)tab[g.B2.slot0] + g.B2.off + sub * g.B2.sub_stride;
@@ -514,7 +522,7 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::BM * Cfg::BN > 64 * 64 ? 2 : 3) 
     return ok;
   };
   if constexpr (EPI == EPI_STORE) {
-    float* C = (float*)tab[g.E.slot] + g.E.off + sub * g.E.sub_stride + (long long)ks * g.E.split_stride;
+    float* C = (float*)(ASUM ? out : tab[g.E.slot]) + g.E.off + sub * g.E.sub_stride + (long long)ks * g.E.split_stride;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll

@@ -519,11 +519,11 @@ __global__ void __launch_bounds__(256) convert_bf16_kernel(void* const* table, i
                                                            int slot_outT16, long long rows, long long cols, int skip_slot,
                                                            const FirstTouch first) {
   void* const* tab = table + (size_t)blockIdx.z * nslots;
-  first_touch(first, blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0);
-  if (skip_slot >= 0 && *(const int*)tab[skip_slot] != 0) return;
+  if (skip_slot >= 0 && *(const int*)tab[skip_slot] != 0) return;   // (a call's first launch has no such slot)
   const float* in = (const float*)first_ptr(first, tab, slot_in);
   uint16_t* out16 = slot_out16 >= 0 ? (uint16_t*)tab[slot_out16] : nullptr;
   uint16_t* outT = slot_outT16 >= 0 ? (uint16_t*)tab[slot_outT16] : nullptr;
+  first_touch(first, blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0);
   __shared__ float tile[64][65];
   const long long row0 = (long long)blockIdx.y * 64, col0 = (long long)blockIdx.x * 64;
   const int t = threadIdx.x;
@@ -562,10 +562,10 @@ template <bool GBF16>
 __global__ void __launch_bounds__(256) sum_bf16_stream_kernel(void* const* table, int nslots, int slot_m, int slot_g, int slot_out16,
                                                               long long count8, const FirstTouch first) {
   void* const* tab = table + (size_t)blockIdx.y * nslots;
-  first_touch(first, blockIdx.x == 0 && blockIdx.y == 0);
   const f32x4_t* M = (const f32x4_t*)first_ptr(first, tab, slot_m);
   const void* G = first_ptr(first, tab, slot_g);
   u32x4_t* out = (u32x4_t*)tab[slot_out16];
+  first_touch(first, blockIdx.x == 0 && blockIdx.y == 0);
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count8; i += stride) {
     f32x4_t a = M[2 * i], b = M[2 * i + 1];
