@@ -1038,11 +1038,9 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
   // team (i mod pr) pc + (j mod pc).
   const int teams = pr * pc, h = 2 * ((int)blockIdx.x - 1) + team, a = h / pc, b = h % pc;
   // Near-diagonal tasks that run at one time go to different workgroups: beside another team's products their own take twice
-  // as long.  Where all of them and all other tiles (which fill the workgroups from the front) have room side by side
-  // they go to the far end, else to the front, whose rows are through first: 8 panels on 7 x 9 70 / 83 us, 16 on 15 x 17 138 / 150,
-  // 24 on 15 x 17 289 / 240, 32 403 / 357 (far end / front).
-  const bool far = 3 * nb + (nb * pc + 1) / 2 <= teams / 2;
-  const int near_h = team * (teams / 2) + (far ? teams / 2 - (int)blockIdx.x : (int)blockIdx.x - 1);
+  // as long.  In which order: see near_order.
+  const int near_x = ((int)blockIdx.x - 1 + p.near_shift) % (teams / 2);
+  const int near_h = team * (teams / 2) + (p.near_far ? teams / 2 - 1 - near_x : near_x);
   auto near_of = [&](int i) __attribute__((always_inline)) {   // which d of row i is this team's (>= 3: none)
     const int d = (near_h - 3 * i) % teams;
     return d < 0 ? d + teams : d;
@@ -1205,7 +1203,7 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
   };
 
   // L[t][.] is read by this team: as row or column of its other tiles, or as row i, i - 2, i - d of a near-diagonal task
-  // (near_of(i + 1) = near_of(i) - 3)
+  // (near_of(i + 1) = near_of(i) - 3; nine teams at least, so that the three rows of a task are told apart)
   const int dt = near_of(t);
   const bool reads_row = t % pr == a || t % pc == b || dt < 3 || dt == 4 || (dt >= 6 && dt < 9);
   int near0 = near_h;   // first near-diagonal task (3 i + d) of the rows that are left
@@ -1286,6 +1284,25 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
   if (FUSE_INV && w_row(nb - 1)) w_diag(nb - 1);   // (row nb - 2 of W has no rows from nb down to go into)
 }
 
+// Workgroup that the near-diagonal tasks of row 0 start at, those of the next rows following from there, three to a row: at the
+// front, at the far end in falling order, or (p.near_shift) in between.  The other tiles fill the workgroups from the
+// front, row by row, once per whole round of 2 pr rows; `beyond` workgroups hold the rows after the last whole round as well.
+//   less than a round: where all near-diagonal tasks and all other tiles have room side by side the former go to the far end, else
+//     to the front, whose rows are through first: 8 panels on 7 x 9 70 / 83 us, 16 on 15 x 17 138 / 150, 24 on 15 x 17 289 /
+//     240, 32 403 / 357 (far end / front).
+//   a round and more, a workgroup for every task: behind the `beyond` ones, where these would get two fifths of the tasks and more:
+//     36 panels on 15 x 17 468 / 437, 40 601 / 556, 44 750 / 676, 48 840 / 768, 52 947 / 925, 20 on 7 x 9 279 / 273;
+//     below that the front: 16 on 7 x 9 190 / 201 (front / behind).
+//   more tasks than workgroups: far end, where the last rows' second tasks then lie beside no row beyond the round: 23 panels on
+//     7 x 9 382 / 368, 25 444 / 408, 31 698 / 665, 33 822 / 746, without such room 26 459 / 484, 28 541 / 567 (front / far end).
+//     On 3 x 5 the front: 7 panels 81 / 86, 13 246 / 251.
+void near_order(CholStreamArgs& p) {
+  const int nb = p.rp / CB, groups = p.pr * p.pc, round = 2 * p.pr, tasks = 3 * nb, beyond = ((nb % round) * p.pc + 1) / 2;
+  p.near_far = beyond > 0 && (nb < round ? tasks + beyond <= groups
+                                         : groups >= 63 && tasks > groups && tasks < 2 * groups && tasks - groups + beyond <= groups);
+  p.near_shift = nb > round && tasks <= groups && 5 * beyond >= 2 * tasks ? groups - beyond : 0;
+}
+
 hipError_t launch_chol_stream(CholStreamArgs p, int batch, hipStream_t s) {
   // 32 KB of unused dynamic LDS on top of the 52 KB the kernel declares: one workgroup per compute unit, so the
   // workgroup on the critical chain shares its unit with nobody
@@ -1293,6 +1310,8 @@ hipError_t launch_chol_stream(CholStreamArgs p, int batch, hipStream_t s) {
     // (102 KB of LDS: more than half of a compute unit's, so one workgroup each)
     // (the inverse needs a flag word per tile of W, and its waits one thread per panel; measured up to 64 panels)
     if (p.vflag_off > 0 && p.rp / CB > FUSED_INV_MAX_NB) return hipErrorInvalidValue;
+    if (2 * p.pr * p.pc < 9) return hipErrorInvalidValue;   // (what `reads_row` takes for granted)
+    near_order(p);
     auto go = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(p.pr * p.pc + 1, batch), dim3(512), 0, s, p);
       return hipGetLastError();

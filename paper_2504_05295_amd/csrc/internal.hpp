@@ -247,6 +247,7 @@ struct CholStreamArgs {
   const float* thr;        // as in CholPanelPtrs
   int* nullmask;
   float* T;                // chain only: scratch, rp x rp per matrix (`stride` words apart)
+  int near_far = 0, near_shift = 0;   // chain only, set by the launcher: order of the near-diagonal tasks
   int chain;               // 1: one more workgroup, number 0, carries the whole chain of diagonal blocks (pr x pc helpers)
   int vflag_off;           // chain only: > 0: the helpers form W = L^-1 as well (no inverse pass afterwards), and (rp / 64)^2
                            // flag words for it start this many 64-bit words into the matrix' sync array; 0: they do not
