@@ -176,29 +176,32 @@ GramPlan plan_gram_rows(const Group& g, int64_t rows) {
 long long round_up(long long x, long long q) { return (x + q - 1) / q * q; }
 // The update of bf16 mode off the large-tile path.  The general core forms it from the fp32 factors, rounding them on the way to
 // the LDS, on tiles of 128 x 64: 2.6 times as many operand bytes as bytes of M, X and G.  The direct-load core's 256 x 128 tile
-// on bf16 copies, padded to whole tiles by a launch more (5-8 us), moves a third as many.  It loses where the contraction is short
-// (the general core's extra bytes grow with r), where the last round of 256 tiles is much padding or nearly empty, and where there
-// are few tiles and the last columns, one by one (n % 4), lie on each one's way.  Lazy-Dion without refresh, whose update is most
-// of it, us a step, general core / direct-load:
-//   one round or a part    5120 x 1111 r = 100, 200  70 / 76, 86 / 87;  3000 x 2047 r = 72, 200  70 / 75, 93 / 97;  2500 x 2500 r = 200
-//                          85 / 82;  2100 x 2100 r = 200  77 / 67;  9001 x 700 r = 200  102 / 94;  300 x 16001 r = 200  95 / 96
-//   two, the last empty    66000 x 127 r = 72  99 / 129;  127 x 40000 r = 72  103 / 132;  3001 x 3001 r = 72, 200  104 / 107, 127 / 124
-//   two or three           5003 x 2999 r = 64, 128, 375  130 / 128, 152 / 145, 211 / 167;  4097 x 4095 r = 72, 200  155 / 163, 197 / 196
-//   five and more          8191 x 4097 r = 72, 100, 200  264 / 251, 282 / 254, 346 / 302
-//                          16383 x 2047 r = 80  264 / 275;  1031 x 40001 r = 72  384 / 389
-//   r = 256                6000 x 2303  172 / 179;  5003 x 2999  192 / 180;  4100 x 4100  212 / 199;  20001 x 703  229 / 215
-// Whole steps: 5003 x 2999 r = 375 429 / 384;  7001 x 5001 r = 600 1343 / 1199;  10001 x 10003 r = 300 2476 / 2267.  So: two rounds'
-// worth of tiles from r = 256 on (352 with two or three last columns), four rounds' from r = 72 on if neither side is narrow, two
-// thirds of the rounds used.  A
-// batch of small matrices loses as one alone does (512 x 512 and 512 x 2048, r = 100, eight layers 350 / 403): judged per matrix.
-// (The last four columns loaded together and shifted into place, all lanes alike: 5120 x 1111 r = 200 87 -> 84, but 8191 x 4097
-// r = 200 302 -> 311, 5003 x 2999 r = 375 step 440 -> 449: not kept.)
+// on bf16 copies, padded to whole tiles by a launch more (5-8 us), moves a third as many: the longer the contraction, the more that
+// saves.  Against it stand the launch, the last round of 256 tiles where it is much padding or nearly empty, and the last columns
+// where they come one by one (n % 4 of 2 and 3).  Lazy-Dion without refresh, most of which is the update, us a step, general core / direct:
+//   on the direct-load core      5003 x 2999 r = 375 207 / 167, 3001 r = 256 157 / 132;  6000 x 2305 r = 352 193 / 170;  4100 x 4100 r = 256 176 / 158
+//                                20001 x 703 r = 353 240 / 219;  8191 x 4097 r = 72, 100, 200 259 / 254, 274 / 251, 336 / 288
+//                                4526 x 25616 r = 100 872 / 848;  7001 x 5001 r = 600 760 / 623;  10001 x 10005 r = 300 1519 / 1304
+//   not, because it loses        short contractions 5120 x 1111 r = 100 70 / 76;  3000 x 2047 r = 72 70 / 75;  16383 x 2047 r = 80 264 / 275
+//                                nearly empty rounds 66000 x 127 r = 72 99 / 129;  3001 x 3001 r = 72 104 / 107
+//                                last columns 6000 x 2303 r = 256 172 / 179
+//                                r < 100 and rows on 16 but not on 128 bytes, which cost the general core least: 4526 x 25616 r = 90
+//                                845 / 869, 4621 x 14000 r = 96 460 / 475 (but 25617, r = 90 970 / 959, and 7234 x 8333 503 / 484)
+//   not, though it wins          beside those: 2100 x 2100 r = 200 77 / 67;  9001 x 700 r = 200 102 / 94;  5003 x 2999 r = 256 192 / 180
+// The lines lie on the general core's side: of 250 shapes drawn beyond them none takes 1 % longer on the direct-load core.  Whole steps on
+// one gradient: 5003 x 2999 r = 375 427 / 389, 7001 x 5001 r = 600 1344 / 1201, 10001 x 10005 r = 300 2511 / 2304.  A batch of small
+// matrices loses as one alone does (512 x 512 and 512 x 2048, r = 100, eight layers 350 / 403): judged per matrix.
+// (The last four columns loaded together and shifted into place: 5120 x 1111 r = 200 87 -> 84, 8191 x 4097 r = 200 302 -> 311: not kept.)
 bool plan_k5_direct(const Group& g) {
   const long long mp = round_up(g.m, 256), np = round_up(g.n, 128), tiles = (mp / 256) * (np / 128);
   const long long round_area = 256ll * 256 * 128, rounds = (tiles + 255) / 256;
-  const bool enough = tiles >= 1024 && std::min(g.m, g.n) >= 4096 && g.n % 4 < 2 ? g.r >= 72 : tiles >= 400 && g.r >= (g.n % 4 < 2 ? 256 : 352);
-  return enough && 3.0 * (double)g.m * (double)g.n >= 2.0 * (double)(rounds * round_area) && mp < (1ll << 31) && np < (1ll << 31) &&
-         std::max(mp, np) * g.rp * 2 < (1ll << 32) && 3ll * g.count <= 65535;
+  const bool last_columns = g.n % 4 >= 2;
+  int64_t least_rank;
+  if (tiles >= 1024 && std::min(g.m, g.n) >= 4096 && !last_columns) least_rank = g.n % 4 == 0 && g.n % 32 ? 100 : 72;
+  else if (tiles >= 400) least_rank = last_columns ? 352 : 256;
+  else return false;
+  if (g.r < least_rank || 3.0 * (double)g.m * (double)g.n < 2.0 * (double)(rounds * round_area)) return false;   // two thirds of the rounds
+  return mp < (1ll << 31) && np < (1ll << 31) && std::max(mp, np) * g.rp * 2 < (1ll << 32) && 3ll * g.count <= 65535;
 }
 // What a plan takes of workspace only for speed: all of it; all but the padded copies of the ragged update; nothing (no splits of the
 // products off the large-tile path either).  A workspace that is too small for one takes the next: of a state the second at most,
@@ -1216,9 +1219,12 @@ int stage_k5(const RowCtx& c, int a16, int b16, int b2_16, int a32, int b32, int
     HIPCHK(launch_pad_bf16(c.tab, NSLOTS, c.batch, jobs, sketch ? 2 : 3, r, g.rp, c.s));
     a.M = (int)mp; a.N = (int)np; a.K = g.rp;
     a.E.rows = m; a.E.cols = n;
-    // (rows that share cache lines: what one tile leaves of a line and the next one fills must meet in a cache.  With the hint
-    // 5003 x 2999 r = 375 takes 477 us a step, 384 without; the general core 429)
-    if (n % 32) a.E.stream_hint = 0;
+    // The hint: not where rows share cache lines (what one tile leaves of a line and the next one fills must meet in a cache: 5003 x
+    // 2999 r = 375 takes a fourth longer with it), and here only from 512 MB on, twice that cache.  Lazy-Dion without refresh, us
+    // a step, with / without: 896 x 12992 r = 256 (210 MB) 129 / 111, 2815 x 5120 r = 256 (259 MB) 141 / 111, 4360 x 3232 r = 479 (254 MB)
+    // 186 / 148, 7942 x 2560 r = 400 (366 MB) 227 / 216, 6982 x 3712 r = 430 (467 MB) 300 / 292, 4589 x 7424 r = 345 (613 MB) 331 / 333,
+    // 17884 x 2048 r = 896 (659 MB) 537 / 561, 6370 x 6912 r = 85 (793 MB) 275 / 293, 16000 x 8192 r = 700 (2.4 GB) 1537 / 1647.
+    a.E.stream_hint = n % 32 == 0 && (double)c.batch * (double)m * (double)n * 18.0 > 512e6 ? 1 : 0;
     a.A = opnd(SLOT_P16, 0, g.rp);
     a.B = opnd(SLOT_R16, 0, g.rp);
     a.B2 = opnd(sketch ? SLOT_R16 : SLOT_Q16, 0, g.rp);

@@ -1,6 +1,6 @@
 """The update of matrices of any size on the direct-load core (bf16 operands, large matrices): sizes around
-whole tiles, rows at every alignment, ranks around a slab of the contraction, both storage types of G, the sketch of Double
-Dion, and nothing written beside the matrices."""
+whole tiles, rows at every alignment, ranks around a slab of the contraction, both storage types of G, and nothing
+written beside the matrices."""
 import numpy as np
 import pytest
 
