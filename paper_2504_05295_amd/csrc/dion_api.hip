@@ -60,7 +60,7 @@ void plan_chol_grid(int cus, int batch, int nb, int* pr, int* pc, int* chain) {
   if (cus < 1 || batch < 1 || nb < 4 || nb > 128) return;
   // From two workgroups per matrix on the single launch still beats a launch per panel, in which every workgroup redoes
   // the diagonal block and the second pass costs a launch per panel to skip.  With sixteen and more per matrix one of
-  // them carries the whole chain of diagonal blocks and the others (pr x pc, coprime) help.
+  // them carries the whole chain of diagonal blocks and the others (pr x pc, each two teams) help.
   const int per = cus / batch;
   if (per >= 256 && nb >= 16) { *pr = 15; *pc = 17; *chain = 1; }
   else if (per >= 64) { *pr = 7; *pc = 9; *chain = 1; }
