@@ -16,6 +16,7 @@
 // Inside a workgroup the diagonal block is the latency-critical part: three waves share it (chol_block.hpp), wave 3
 // meanwhile fetches the two panel blocks C21_i, C21_j into LDS.
 #include "chol_block.hpp"
+#include "chol_order.hpp"
 
 namespace dion {
 
@@ -1284,25 +1285,6 @@ __global__ void __launch_bounds__(512, 2) chol_chain_kernel(CholStreamArgs p) {
   if (FUSE_INV && w_row(nb - 1)) w_diag(nb - 1);   // (row nb - 2 of W has no rows from nb down to go into)
 }
 
-// Workgroup that the near-diagonal tasks of row 0 start at, those of the next rows following from there, three to a row: at the
-// front, at the far end in falling order, or (p.near_shift) in between.  The other tiles fill the workgroups from the
-// front, row by row, once per whole round of 2 pr rows; `beyond` workgroups hold the rows after the last whole round as well.
-//   less than a round: where all near-diagonal tasks and all other tiles have room side by side the former go to the far end, else
-//     to the front, whose rows are through first: 8 panels on 7 x 9 70 / 83 us, 16 on 15 x 17 138 / 150, 24 on 15 x 17 289 /
-//     240, 32 403 / 357 (far end / front).
-//   a round and more, a workgroup for every task: behind the `beyond` ones, where these would get two fifths of the tasks and more:
-//     36 panels on 15 x 17 468 / 437, 40 601 / 556, 44 750 / 676, 48 840 / 768, 52 947 / 925, 20 on 7 x 9 279 / 273;
-//     below that the front: 16 on 7 x 9 190 / 201 (front / behind).
-//   more tasks than workgroups: far end, where the last rows' second tasks then lie beside no row beyond the round: 23 panels on
-//     7 x 9 382 / 368, 25 444 / 408, 31 698 / 665, 33 822 / 746, without such room 26 459 / 484, 28 541 / 567 (front / far end).
-//     On 3 x 5 the front: 7 panels 81 / 86, 13 246 / 251.
-void near_order(CholStreamArgs& p) {
-  const int nb = p.rp / CB, groups = p.pr * p.pc, round = 2 * p.pr, tasks = 3 * nb, beyond = ((nb % round) * p.pc + 1) / 2;
-  p.near_far = beyond > 0 && (nb < round ? tasks + beyond <= groups
-                                         : groups >= 63 && tasks > groups && tasks < 2 * groups && tasks - groups + beyond <= groups);
-  p.near_shift = nb > round && tasks <= groups && 5 * beyond >= 2 * tasks ? groups - beyond : 0;
-}
-
 hipError_t launch_chol_stream(CholStreamArgs p, int batch, hipStream_t s) {
   // 32 KB of unused dynamic LDS on top of the 52 KB the kernel declares: one workgroup per compute unit, so the
   // workgroup on the critical chain shares its unit with nobody
@@ -1311,7 +1293,9 @@ hipError_t launch_chol_stream(CholStreamArgs p, int batch, hipStream_t s) {
     // (the inverse needs a flag word per tile of W, and its waits one thread per panel; measured up to 64 panels)
     if (p.vflag_off > 0 && p.rp / CB > FUSED_INV_MAX_NB) return hipErrorInvalidValue;
     if (2 * p.pr * p.pc < 9) return hipErrorInvalidValue;   // (what `reads_row` takes for granted)
-    near_order(p);
+    const NearOrder order = near_order(p.rp / CB, p.pr, p.pc);
+    p.near_far = order.far;
+    p.near_shift = order.shift;
     auto go = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(p.pr * p.pc + 1, batch), dim3(512), 0, s, p);
       return hipGetLastError();

@@ -4,12 +4,16 @@ Checked: each update finds the tiles of L it reads finished and is applied once 
 only over finished tiles, a team's wait covers every row it reads, nobody waits for ever, and at the end everything is there.
 A change of ownership, order or flags in the kernel belongs in here too."""
 import random
+import shutil
+import subprocess
 
 import pytest
 
+from paper_2504_05295_amd import build
+
 
 def near_order(nb, pr, pc):
-    """near_order() of the launcher: (shift, far) of the near-diagonal tasks' order over pr * pc helper workgroups"""
+    """near_order() of csrc/chol_order.hpp: (shift, far) of the near-diagonal tasks' order over pr * pc helper workgroups"""
     groups, rounds, tasks = pr * pc, 2 * pr, 3 * nb
     beyond = ((nb % rounds) * pc + 1) // 2
     if nb < rounds:
@@ -236,6 +240,30 @@ def test_order_of_near_diagonal_tasks(grid):
         if shift or (far and nb < 2 * pr):
             # as many tasks as there are workgroups without rows beyond the last whole round lie on those
             assert len(held - set(range(beyond))) == min(len(held), groups - beyond), (nb, len(held))
+
+
+def test_rule_is_the_launchers(tmp_path):
+    compiler = shutil.which("g++") or shutil.which("c++")
+    if compiler is None:
+        pytest.skip("no C++ compiler")
+    source = tmp_path / "order.cpp"
+    source.write_text("""#include <cstdio>
+#include "chol_order.hpp"
+int main() {
+  const int grids[3][2] = {{3, 5}, {7, 9}, {15, 17}};
+  for (auto& g : grids)
+    for (int nb = 4; nb <= 128; ++nb) {
+      const dion::NearOrder o = dion::near_order(nb, g[0], g[1]);
+      std::printf("%d %d %d %d %d\\n", nb, g[0], g[1], o.shift, (int)o.far);
+    }
+}
+""")
+    subprocess.run([compiler, "-std=c++17", "-I", build.CSRC, str(source), "-o", str(tmp_path / "order")], check=True)
+    lines = subprocess.run([str(tmp_path / "order")], check=True, capture_output=True, text=True).stdout.split("\n")[:-1]
+    assert len(lines) == 3 * 125
+    for line in lines:
+        nb, pr, pc, shift, far = map(int, line.split())
+        assert near_order(nb, pr, pc) == (shift, bool(far)), line
 
 
 @pytest.mark.parametrize("mistake", ["chain ignores the third flag", "second row of a task not waited for"])
